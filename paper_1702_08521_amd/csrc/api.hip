@@ -64,8 +64,8 @@ Layout layout_of(const slmpp_grid_desc& d) {
   L.bufA = take(sizeof(double2) * nxs);
   L.bufB = take(sizeof(double2) * nxs);
   L.tw = take(sizeof(double2) * sumnx);
-  L.partials = take(sizeof(double) * kDiagBlocks * 5);
-  L.diagfield = take(sizeof(double) * 4);
+  L.partials = take(sizeof(double) * kDiagPartials);
+  L.diagfield = take(sizeof(double) * 8);
   int64_t maxnv = 1;
   for (int l = 0; l < d.D; ++l) maxnv = std::max<int64_t>(maxnv, d.nv[l]);
   L.table = take(pencil_table_bytes(SLMPP_F64, std::max<int64_t>(maxnv, nxs)));
@@ -906,7 +906,8 @@ slmpp_status slmpp_velocity_moments(slmpp_ctx* c, double* rho_dev, double* mean_
   if (!rho_dev || !mean_dev || !disp_dev)
     return c->fail(SLMPP_ERR_INVALID, "rho_dev, mean_dev and disp_dev must be non-NULL");
   hipError_t e = launch_velocity_moments(c->d.storage, c->f, c->D, c->d.nv, c->d.v_lo, c->hv,
-                                         c->nxs, rho_dev, mean_dev, disp_dev, c->stream);
+                                         c->nxs, rho_dev, mean_dev, disp_dev, c->stage(),
+                                         c->lay.stage_doubles, c->stream);
   if (e != hipSuccess) return c->hip_fail(e, "velocity moments launch");
   return SLMPP_OK;
 }
@@ -917,7 +918,7 @@ slmpp_status slmpp_velocity_distribution(slmpp_ctx* c, double* F_dev) {
   double xvol = 1.0;
   for (int l = 0; l < c->D; ++l) xvol *= c->hx[l];
   hipError_t e = launch_velocity_distribution(c->d.storage, c->f, c->nxs, c->nvs, xvol, F_dev,
-                                              c->stream);
+                                              c->stage(), c->lay.stage_doubles, c->stream);
   if (e != hipSuccess) return c->hip_fail(e, "velocity distribution launch");
   return SLMPP_OK;
 }
@@ -1018,43 +1019,26 @@ slmpp_status slmpp_diag(slmpp_ctx* c, slmpp_diag_out* out) {
   slmpp_status st = SLMPP_OK;
   if (!c->field_valid) st = c->field();
   if (st != SLMPP_OK) return st;
-  const int nb = kDiagBlocks;
-  hipError_t e = launch_diag_f(c->d.storage, c->f, c->ncell, c->partials(), nb, c->stream);
   int64_t inner1 = 1;
   for (int l = 1; l < c->D; ++l) inner1 *= c->d.nx[l];
+  hipError_t e = launch_diag(c->d.storage, c->f, c->ncell, c->accel(), c->D, c->nxs, c->d.nx[0], inner1,
+                             c->partials(), c->diagfield(), c->stream);
+  double r[7];
   if (e == hipSuccess)
-    e = launch_diag_field(c->accel(), c->D, c->nxs, c->d.nx[0], inner1, c->diagfield(), c->stream);
-  std::vector<double> part(nb * 5);
-  double fld[3];
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(part.data(), c->partials(), sizeof(double) * nb * 5, hipMemcpyDeviceToHost,
-                       c->stream);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(fld, c->diagfield(), sizeof(double) * 3, hipMemcpyDeviceToHost, c->stream);
+    e = hipMemcpyAsync(r, c->diagfield(), sizeof(r), hipMemcpyDeviceToHost, c->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
   if (e != hipSuccess) return c->hip_fail(e, "diag");
-  double s = 0.0, comp = 0.0, mn = INFINITY, mx = -INFINITY, bad = 0.0;
-  for (int b = 0; b < nb; ++b) {
-    const double x = part[b * 4 + 0];
-    const double t = s + x;
-    comp += (std::fabs(s) >= std::fabs(x)) ? (s - t) + x : (x - t) + s;
-    s = t;
-    comp += part[b * 4 + 1];
-    mn = std::min(mn, part[b * 4 + 2]);
-    mx = std::max(mx, part[b * 4 + 3]);
-    bad += part[nb * 4 + b];
-  }
   double vol = 1.0, dxv = 1.0;
   for (int l = 0; l < c->D; ++l) {
     vol *= c->hx[l] * c->hv[l];
     dxv *= c->hx[l];
   }
-  out->mass = vol * (s + comp);
-  out->f_min = mn;
-  out->f_max = mx;
-  out->nonfinite = (int64_t)bad;
-  out->field_energy = 0.5 * fld[0] * dxv;
-  out->mode_amp = std::sqrt(fld[1] * fld[1] + fld[2] * fld[2]) / (double)c->nxs;
+  out->mass = vol * r[0];
+  out->f_min = r[1];
+  out->f_max = r[2];
+  out->nonfinite = (int64_t)r[3];
+  out->field_energy = 0.5 * r[4] * dxv;
+  out->mode_amp = std::sqrt(r[5] * r[5] + r[6] * r[6]) / (double)c->nxs;
   return SLMPP_OK;
 }
 

@@ -3,6 +3,7 @@
 // reductions for diagnostics.  All field arithmetic is double precision.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdint>
 #include <type_traits>
@@ -103,137 +104,343 @@ __global__ void __launch_bounds__(NT) moment_kernel(const T* __restrict__ f, int
   if (threadIdx.x == 0) rho[blockIdx.x] = dvol * (tot.s + tot.c);
 }
 
-// Velocity moments of one spatial cell per workgroup (Sec. 2.3): density,
-// mean velocity and dispersion per velocity axis, two passes over the
-// cell's contiguous velocity block (the second re-reads it from cache);
-// compensated double sums of plain sums over groups of eight elements.
-template <typename T, int NT, int D>  // D: velocity axes (a constant: the loops over
-                                      // axes unroll and every accumulator stays in registers)
-__global__ void __launch_bounds__(NT) velocity_moments_kernel(const T* __restrict__ f, int,
-                                                              int64_t nvs, int3 nv, double3 vlo,
-                                                              double3 dv, double dvol, int64_t nxs,
-                                                              double* __restrict__ rho,
-                                                              double* __restrict__ mean,
-                                                              double* __restrict__ disp) {
-  const T* b = f + (int64_t)blockIdx.x * nvs;
-  const int n[3] = {nv.x, nv.y, nv.z};
-  const double lo[3] = {vlo.x, vlo.y, vlo.z}, h[3] = {dv.x, dv.y, dv.z};
-  // velocity index of element k as digits (last axis fastest): the digits
-  // of this thread's first element and of the stride NT, then a digit-wise
-  // add with carries per step instead of a division per element
-  int j0[3] = {0, 0, 0}, st[3] = {0, 0, 0};
-  {
-    int64_t rem = threadIdx.x, str = NT;
-    for (int l = D - 1; l >= 0; --l) {
-      j0[l] = (int)(rem % n[l]);
-      rem /= n[l];
-      st[l] = (int)(str % n[l]);
-      str /= n[l];
-    }
-  }
-  int j[3];
-  auto restart = [&]() {
-    for (int l = 0; l < 3; ++l) j[l] = j0[l];
-  };
-  auto centres = [&](double* v) {
-    for (int l = 0; l < D; ++l) v[l] = lo[l] + ((double)j[l] + 0.5) * h[l];
-  };
-  auto next = [&]() {  // j += st; past the last element the digits are unused
-    int carry = 0;
-    for (int l = D - 1; l >= 0; --l) {
-      j[l] += st[l] + carry;
-      carry = j[l] >= n[l];
-      if (carry) j[l] -= n[l];
-    }
-  };
-  // each thread adds groups of up to kGroup of its elements plainly and
-  // feeds the group sums to the compensated accumulators
-  constexpr int kGroup = 8;
-  KSum s0{0.0, 0.0}, s1[3] = {{0.0, 0.0}, {0.0, 0.0}, {0.0, 0.0}};
-  double p0 = 0.0, p1[3] = {0.0, 0.0, 0.0};
-  int cnt = 0;
-  restart();
-  for (int64_t k = threadIdx.x; k < nvs; k += NT, next()) {
-    double v[3];
-    centres(v);
-    const double x = (double)b[k];
-    p0 += x;
-    for (int l = 0; l < D; ++l) p1[l] += x * v[l];
-    if (++cnt == kGroup) {
-      kadd(s0, p0);
-      for (int l = 0; l < D; ++l) kadd(s1[l], p1[l]);
-      p0 = 0.0;
-      for (int l = 0; l < D; ++l) p1[l] = 0.0;
-      cnt = 0;
-    }
-  }
-  kadd(s0, p0);
-  for (int l = 0; l < D; ++l) kadd(s1[l], p1[l]);
-  const KSum t0 = block_ksum<NT>(s0);
-  const double m0 = t0.s + t0.c;
-  double u[3] = {0.0, 0.0, 0.0};
-  for (int l = 0; l < D; ++l) {
-    const KSum t1 = block_ksum<NT>(s1[l]);
-    u[l] = m0 != 0.0 ? (t1.s + t1.c) / m0 : 0.0;
-  }
-  KSum s2[3] = {{0.0, 0.0}, {0.0, 0.0}, {0.0, 0.0}};
-  double p2[3] = {0.0, 0.0, 0.0};
-  cnt = 0;
-  restart();
-  for (int64_t k = threadIdx.x; k < nvs; k += NT, next()) {
-    double v[3];
-    centres(v);
-    const double x = (double)b[k];
-    for (int l = 0; l < D; ++l) {
-      const double d = v[l] - u[l];
-      p2[l] += x * d * d;
-    }
-    if (++cnt == kGroup) {
-      for (int l = 0; l < D; ++l) {
-        kadd(s2[l], p2[l]);
-        p2[l] = 0.0;
-      }
-      cnt = 0;
-    }
-  }
-  for (int l = 0; l < D; ++l) kadd(s2[l], p2[l]);
-  for (int l = 0; l < D; ++l) {
-    const KSum t2 = block_ksum<NT>(s2[l]);
-    if (threadIdx.x == 0) {
-      mean[(int64_t)l * nxs + blockIdx.x] = u[l];
-      disp[(int64_t)l * nxs + blockIdx.x] = m0 != 0.0 ? (t2.s + t2.c) / m0 : 0.0;
-    }
-  }
-  if (threadIdx.x == 0) rho[blockIdx.x] = dvol * m0;
+// Exact addition: a.s + x as s plus its rounding error in c (Knuth's
+// two-sum, no comparison of the magnitudes).
+__device__ __forceinline__ void kadd2(KSum& a, double x) {
+  const double t = a.s + x;
+  const double b = t - a.s;
+  a.c += (a.s - (t - b)) + (x - b);
+  a.s = t;
+}
+__device__ __forceinline__ void kmerge2(KSum& a, const KSum& b) {
+  kadd2(a, b.s);
+  a.c += b.c;
 }
 
-// F[k] = xvol * sum_x f[x][k]: one thread per velocity cell.  Few threads
-// walk long columns here (one per velocity cell), so each keeps 16 loads in
-// flight: rows x = 16 m + r go to accumulator r % 4, merged in a fixed order.
+// 16-byte vectors at element-aligned addresses (the hardware takes global
+// vector accesses at any 4-byte address)
+template <typename T>
+struct UVec;
+template <>
+struct UVec<float> {
+  typedef float type __attribute__((ext_vector_type(4), aligned(4)));
+  static constexpr int N = 4;
+};
+template <>
+struct UVec<double> {
+  typedef double type __attribute__((ext_vector_type(2), aligned(8)));
+  static constexpr int N = 2;
+};
+// the vector at p, of which only the first `valid` elements exist (zeros for the rest)
+template <typename T>
+__device__ __forceinline__ typename UVec<T>::type load_part(const T* p, int64_t valid) {
+  using V = typename UVec<T>::type;
+  constexpr int VN = UVec<T>::N;
+  if (valid >= VN) return __builtin_nontemporal_load(reinterpret_cast<const V*>(p));
+  V v{};
+#pragma unroll
+  for (int c = 0; c < VN; ++c)
+    if (c < valid) v[c] = p[c];
+  return v;
+}
+
+// Velocity moments of one spatial cell per workgroup (Sec. 2.3): density,
+// mean velocity and dispersion per velocity axis, from one read of the
+// cell's velocity block.  The block [n1][n2][n3] (n1 = 1 for one velocity
+// axis, n3 = 1 for two) is summed to its marginals M_l(j_l) in LDS, and mean
+// and dispersion of axis l come from M_l alone (two passes over n_l numbers,
+// so nothing cancels that did not cancel in two passes over f).
+//
+// Bound by the read of f (and, with short planes, by the latency of its
+// bursts of loads): one pass instead of two, 16-byte loads and sums without
+// index arithmetic took 24^3 x 40^3 FP32 (3.5 GB) from 2414 to 868 us.
+// A wavefront takes whole planes j1, its lanes the plane's 16-byte vectors
+// (kMomVec per lane; what is left of a plane, or a plane narrower than a
+// wavefront, is taken several j1 at a time) and kMomPlanes planes per burst
+// of loads: the plane sums go to M_1(j1), and the lanes' running sums over j1
+// give the marginal over (j2, j3) of the chunk, which is folded into M_2 and
+// M_3.  Sums over more than a few values are compensated.  Held to 128
+// VGPRs: at three wavefronts per SIMD instead of four it took 958 us; four
+// vectors per lane and two planes per burst 970 us, the wavefronts of a
+// workgroup sharing one spatial cell 1118 us.
+// GLOB: the marginals in `marg` instead of LDS (axes too long for it).
+constexpr int kMomVec = 2;
+constexpr int kMomPlanes = 4;
+template <typename T, int NT, bool GLOB>
+__global__ void __attribute__((amdgpu_flat_work_group_size(1, NT), amdgpu_waves_per_eu(4)))
+velocity_moments_kernel(const T* __restrict__ f, int D, int n1,
+                                                              int n2, int n3, double3 vlo, double3 dv,
+                                                              double dvol, int64_t nxs,
+                                                              double* __restrict__ rho,
+                                                              double* __restrict__ mean,
+                                                              double* __restrict__ disp,
+                                                              KSum* __restrict__ marg) {
+  using V = typename UVec<T>::type;
+  constexpr int VN = UVec<T>::N;
+  constexpr int NW = NT / 64;
+  constexpr int CH = 64 * VN * kMomVec;  // plane elements of a full chunk
+  extern __shared__ __align__(16) unsigned char mom_smem[];
+  // LDS: the wavefronts' marginals over (j2, j3) of the current chunk, the
+  // parts of M_3 of that chunk, and the marginals M_l
+  const int cl = min(CH, n2 * n3);
+  double* W = reinterpret_cast<double*>(mom_smem);
+  double* Q = W + NW * cl;
+  KSum* M1 = reinterpret_cast<KSum*>(Q + max(NT, n3));
+  if constexpr (GLOB) M1 = marg + (int64_t)blockIdx.x * (n1 + n2 + n3);
+  KSum* M2 = M1 + n1;
+  KSum* M3 = M2 + n2;
+  const int np = n2 * n3;
+  const T* b = f + (int64_t)blockIdx.x * n1 * np;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  for (int k = tid; k < n1 + n2 + n3; k += NT) M1[k] = KSum{0.0, 0.0};
+  __syncthreads();
+  for (int c0 = 0; c0 < np; c0 += CH) {
+    // lanes per plane (a power of two) and planes per wavefront pass
+    int lpp = 64;
+    while (lpp > 1 && (lpp / 2) * VN * kMomVec >= np - c0) lpp >>= 1;
+    const int sub = 64 / lpp, sl = lane / lpp, pl = lane & (lpp - 1);
+    KSum acc[kMomVec][VN];
+#pragma unroll
+    for (int k = 0; k < kMomVec; ++k)
+#pragma unroll
+      for (int c = 0; c < VN; ++c) acc[k][c] = KSum{0.0, 0.0};
+    // (loads are unconditional, from the last whole vector of the plane at
+    // most; off[k] says by how many elements vector k was moved down, VN or
+    // more where it has no element of the plane)
+    int ek[kMomVec], off_[kMomVec];
+#pragma unroll
+    for (int k = 0; k < kMomVec; ++k) {
+      const int e = c0 + (pl + k * lpp) * VN;
+      ek[k] = max(0, min(e, np - VN));
+      off_[k] = e - ek[k];
+    }
+    const bool tails = np % VN != 0;
+    for (int j0 = wave * sub + sl; j0 - sl < n1; j0 += kMomPlanes * NW * sub) {
+      // kMomPlanes planes: their loads first, then each element's plain sum
+      // over them into its compensated one
+      V x[kMomPlanes][kMomVec];
+#pragma unroll
+      for (int g = 0; g < kMomPlanes; ++g) {
+        const T* row = b + (int64_t)min(j0 + g * NW * sub, n1 - 1) * np;
+#pragma unroll
+        for (int k = 0; k < kMomVec; ++k) {
+          if (np >= VN)
+            x[g][k] = __builtin_nontemporal_load(reinterpret_cast<const V*>(row + ek[k]));
+          else
+            x[g][k] = load_part(row, np);
+        }
+      }
+      if (tails) {
+#pragma unroll
+        for (int g = 0; g < kMomPlanes; ++g)
+#pragma unroll
+          for (int k = 0; k < kMomVec; ++k)
+#pragma unroll
+            for (int c = 0; c < VN; ++c) {
+              T v = T(0);
+#pragma unroll
+              for (int q = c; q < VN; ++q) v = off_[k] == q - c ? x[g][k][q] : v;
+              x[g][k][c] = v;
+            }
+      }
+      double rs[kMomPlanes];
+#pragma unroll
+      for (int g = 0; g < kMomPlanes; ++g) {
+        rs[g] = 0.0;
+#pragma unroll
+        for (int k = 0; k < kMomVec; ++k)
+          if (off_[k] >= VN || j0 + g * NW * sub >= n1) x[g][k] = V{};
+      }
+#pragma unroll
+      for (int k = 0; k < kMomVec; ++k)
+#pragma unroll
+        for (int c = 0; c < VN; ++c) {
+          double v[kMomPlanes];
+#pragma unroll
+          for (int g = 0; g < kMomPlanes; ++g) {
+            v[g] = (double)x[g][k][c];
+            rs[g] += v[g];
+          }
+          kadd2(acc[k][c], (v[0] + v[1]) + (v[2] + v[3]));
+        }
+      // the planes' sums over the lanes; this wavefront's own M_1(j1)
+      if (lpp == 64) {
+        // four sums at once: halves of the wavefront swap pairs, quarters
+        // single sums, and 16 lanes add up one plane each
+        const bool h = lane & 32, q = lane & 16;
+        double u0 = h ? rs[2] : rs[0], u1 = h ? rs[3] : rs[1];
+        u0 += __shfl_xor(h ? rs[0] : rs[2], 32, 64);
+        u1 += __shfl_xor(h ? rs[1] : rs[3], 32, 64);
+        double u = q ? u1 : u0;
+        u += __shfl_xor(q ? u0 : u1, 16, 64);
+#pragma unroll
+        for (int off = 8; off > 0; off >>= 1) u += __shfl_xor(u, off, 64);
+        const int j1 = j0 + ((h ? 2 : 0) + (q ? 1 : 0)) * NW;
+        if ((lane & 15) == 0 && j1 < n1) kadd2(M1[j1], u);
+      } else {
+#pragma unroll
+        for (int g = 0; g < kMomPlanes; ++g) {
+          for (int off = 1; off < lpp; off <<= 1) rs[g] += __shfl_xor(rs[g], off, 64);
+          const int j1 = j0 + g * NW * sub;
+          if (pl == 0 && j1 < n1) kadd2(M1[j1], rs[g]);
+        }
+      }
+    }
+    // the planes of a wavefront pass, in a fixed order
+    for (int off = lpp; off < 64; off <<= 1)
+#pragma unroll
+      for (int k = 0; k < kMomVec; ++k)
+#pragma unroll
+        for (int c = 0; c < VN; ++c) {
+          const KSum o{__shfl_xor(acc[k][c].s, off, 64), __shfl_xor(acc[k][c].c, off, 64)};
+          kmerge2(acc[k][c], o);
+        }
+    const int ce = min(CH, np - c0);
+    if (sl == 0) {
+#pragma unroll
+      for (int k = 0; k < kMomVec; ++k)
+#pragma unroll
+        for (int c = 0; c < VN; ++c) {
+          const int e = (pl + k * lpp) * VN + c;
+          if (e < ce) W[wave * cl + e] = acc[k][c].s + acc[k][c].c;
+        }
+    }
+    __syncthreads();
+    auto P = [&](int e) {  // marginal at plane element c0 + e
+      double v = W[e];
+#pragma unroll
+      for (int w = 1; w < NW; ++w) v += W[w * cl + e];
+      return v;
+    };
+    // M_2: 16 lanes per row of the chunk; M_3: the rows dealt to as many
+    // parts as there are threads for, then the parts in order
+    const int r0 = c0 / n3, rows = (c0 + ce - 1) / n3 - r0 + 1;
+    for (int q = tid / 16; q < (rows + NT / 16 - 1) / (NT / 16) * (NT / 16); q += NT / 16) {
+      double v = 0.0;
+      if (q < rows) {
+        const int lo = max((r0 + q) * n3, c0) - c0, hi = min((r0 + q + 1) * n3, c0 + ce) - c0;
+        KSum m{0.0, 0.0};
+        for (int e = lo + (tid & 15); e < hi; e += 16) kadd2(m, P(e));
+        v = m.s + m.c;
+      }
+#pragma unroll
+      for (int off = 1; off < 16; off <<= 1) v += __shfl_xor(v, off, 64);
+      if ((tid & 15) == 0 && q < rows) kadd2(M2[r0 + q], v);
+    }
+    const int parts = n3 < NT ? NT / n3 : 1;
+    for (int j = tid; j < parts * n3; j += NT) {
+      const int j3 = j % n3;
+      KSum m{0.0, 0.0};
+      for (int r = r0 + j / n3; r < r0 + rows; r += parts) {
+        const int e = r * n3 + j3 - c0;
+        if (e >= 0 && e < ce) kadd2(m, P(e));
+      }
+      Q[j] = m.s + m.c;
+    }
+    __syncthreads();
+    for (int j3 = tid; j3 < n3; j3 += NT) {
+      KSum m = M3[j3];
+      for (int q = 0; q < parts; ++q) kadd2(m, Q[q * n3 + j3]);
+      M3[j3] = m;
+    }
+  }
+  __syncthreads();
+  // density, then mean and dispersion per axis, axes dealt to the wavefronts
+  for (int ax = wave; ax < D; ax += NW) {
+    const KSum* M = D == 3 ? (ax == 0 ? M1 : ax == 1 ? M2 : M3) : (D == 2 ? (ax == 0 ? M1 : M2) : M2);
+    const int n = D == 3 ? (ax == 0 ? n1 : ax == 1 ? n2 : n3) : (D == 2 ? (ax == 0 ? n1 : n2) : n2);
+    const double lo = ax == 0 ? vlo.x : ax == 1 ? vlo.y : vlo.z;
+    const double h = ax == 0 ? dv.x : ax == 1 ? dv.y : dv.z;
+    auto wave_sum = [&](KSum v) {
+#pragma unroll
+      for (int off = 1; off < 64; off <<= 1) {
+        const KSum o{__shfl_xor(v.s, off, 64), __shfl_xor(v.c, off, 64)};
+        kmerge2(v, o);
+      }
+      return v.s + v.c;
+    };
+    KSum s0{0.0, 0.0}, s1{0.0, 0.0}, s2{0.0, 0.0};
+    for (int j = lane; j < n; j += 64) {
+      const double m = M[j].s + M[j].c;
+      kadd2(s0, m);
+      kadd2(s1, m * (lo + ((double)j + 0.5) * h));
+    }
+    const double m0 = wave_sum(s0), m1 = wave_sum(s1);
+    const double u = m0 != 0.0 ? m1 / m0 : 0.0;
+    for (int j = lane; j < n; j += 64) {
+      const double d = lo + ((double)j + 0.5) * h - u;
+      kadd2(s2, (M[j].s + M[j].c) * d * d);
+    }
+    const double m2 = wave_sum(s2);
+    if (lane == 0) {
+      mean[(int64_t)ax * nxs + blockIdx.x] = u;
+      disp[(int64_t)ax * nxs + blockIdx.x] = m0 != 0.0 ? m2 / m0 : 0.0;
+      if (ax == 0) rho[blockIdx.x] = dvol * m0;
+    }
+  }
+}
+
+// F[k] = xvol * sum_x f[x][k]: a thread walks the spatial cells of its
+// share (grid.y shares) for one 16-byte vector of velocity cells, eight rows
+// in flight, every velocity cell's sum compensated.  With one share the
+// thread writes F; with several, each writes its sums to part[share][k] and
+// distribution_sum_kernel adds them in order.  (One share only was bound by
+// the few workgroups of a small velocity grid: 16 for 64^2 velocity cells;
+// 24^3 x 40^3 FP32 took 789 us, now 574 + 13 us.)
 template <typename T>
 __global__ void __launch_bounds__(256) velocity_distribution_kernel(const T* __restrict__ f,
                                                                     int64_t nxs, int64_t nvs,
                                                                     double xvol,
-                                                                    double* __restrict__ F) {
-  constexpr int U = 16;
-  for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < nvs;
-       k += (int64_t)gridDim.x * blockDim.x) {
-    KSum a[4] = {{0.0, 0.0}, {0.0, 0.0}, {0.0, 0.0}, {0.0, 0.0}};
+                                                                    double* __restrict__ F,
+                                                                    KSum* __restrict__ part) {
+  using V = typename UVec<T>::type;
+  constexpr int VN = UVec<T>::N, U = 8;
+  const int64_t per = (nxs + gridDim.y - 1) / gridDim.y;
+  const int64_t x0 = blockIdx.y * per, x1 = min(nxs, x0 + per);
+  const int64_t nvec = (nvs + VN - 1) / VN;
+  for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < nvec;
+       q += (int64_t)gridDim.x * blockDim.x) {
+    const int64_t k = q * VN;
     const T* col = f + k;
-    int64_t ix = 0;
-    for (; ix + U <= nxs; ix += U) {
-      T x[U];
+    KSum a[VN];
 #pragma unroll
-      for (int u = 0; u < U; ++u) x[u] = col[(ix + u) * nvs];
+    for (int c = 0; c < VN; ++c) a[c] = KSum{0.0, 0.0};
+    int64_t ix = x0;
+    if (nvs - k >= VN) {
+      for (; ix + U <= x1; ix += U) {
+        V x[U];
 #pragma unroll
-      for (int u = 0; u < U; ++u) kadd(a[u % 4], (double)x[u]);
+        for (int u = 0; u < U; ++u)
+          x[u] = __builtin_nontemporal_load(reinterpret_cast<const V*>(col + (ix + u) * nvs));
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+          for (int c = 0; c < VN; ++c) kadd2(a[c], (double)x[u][c]);
+      }
     }
-    for (; ix < nxs; ++ix) kadd(a[0], (double)col[ix * nvs]);
-    kmerge(a[0], a[1]);
-    kmerge(a[2], a[3]);
-    kmerge(a[0], a[2]);
-    F[k] = xvol * (a[0].s + a[0].c);
+    for (; ix < x1; ++ix) {
+      const V x = load_part(col + ix * nvs, nvs - k);
+#pragma unroll
+      for (int c = 0; c < VN; ++c) kadd2(a[c], (double)x[c]);
+    }
+#pragma unroll
+    for (int c = 0; c < VN; ++c)
+      if (k + c < nvs) {
+        if (part)
+          part[blockIdx.y * nvs + k + c] = a[c];
+        else
+          F[k + c] = xvol * (a[c].s + a[c].c);
+      }
   }
+}
+__global__ void __launch_bounds__(256) distribution_sum_kernel(const KSum* __restrict__ part,
+                                                               int shares, int64_t nvs, double xvol,
+                                                               double* __restrict__ F) {
+  const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (k >= nvs) return;
+  KSum a{0.0, 0.0};
+  for (int y = 0; y < shares; ++y) kmerge2(a, part[y * nvs + k]);
+  F[k] = xvol * (a.s + a.c);
 }
 
 // rho[i * ncol + c] = dvol * sum_q part[(c * nsub + q) * n + i]; thread
@@ -427,25 +634,141 @@ __global__ void to_double_kernel(const T* __restrict__ f, double* __restrict__ d
 }
 
 // ---- diagnostics --------------------------------------------------------
-// partials[b*4 + 0..3] = (sum, compensation, min, max) and
-// partials[nblocks*4 + b] = count of non-finite values, per block b.
+// partials[b*5 + 0..4] = (sum, compensation, min, max, number of non-finite
+// values) of block b; non-finite values enter nothing else.  Bound by the
+// read of f: 16-byte loads, four in flight per thread (one 4-byte load at a
+// time read 24^3 x 40^3 FP32 at 1.8 TB/s in 1989 us; now 609 us,
+// 5.8 TB/s).  A
+// vector's elements are tested together through their sum, and one by one
+// only where that is not finite.
 template <typename T, int NT>
 __global__ void __launch_bounds__(NT) diag_f_kernel(const T* __restrict__ f, int64_t n,
                                                     double* __restrict__ partials) {
+  using V = typename UVec<T>::type;
+  constexpr int VN = UVec<T>::N, U = 4;
   KSum acc{0.0, 0.0};
-  double mn = INFINITY, mx = -INFINITY;
+  T mn = (T)INFINITY, mx = -(T)INFINITY;
   double bad = 0.0;
-  for (int64_t t = (int64_t)blockIdx.x * NT + threadIdx.x; t < n; t += (int64_t)gridDim.x * NT) {
-    const double v = (double)f[t];
-    if (!isfinite(v)) {
+  auto one = [&](T x) {
+    if (!isfinite(x)) {
       bad += 1.0;
-      continue;
+      return;
     }
-    kadd(acc, v);
-    mn = fmin(mn, v);
-    mx = fmax(mx, v);
+    kadd2(acc, (double)x);
+    mn = x < mn ? x : mn;
+    mx = x > mx ? x : mx;
+  };
+  auto vec = [&](V x) {
+    double t = (double)x[0];
+#pragma unroll
+    for (int c = 1; c < VN; ++c) t += (double)x[c];
+    if (!isfinite(t)) {
+#pragma unroll
+      for (int c = 0; c < VN; ++c) one(x[c]);
+      return;
+    }
+    if constexpr (VN == 4) {
+      kadd2(acc, t);  // four floats: exact in double to its last bits
+    } else {
+#pragma unroll
+      for (int c = 0; c < VN; ++c) kadd2(acc, (double)x[c]);
+    }
+#pragma unroll
+    for (int c = 0; c < VN; ++c) {
+      mn = x[c] < mn ? x[c] : mn;
+      mx = x[c] > mx ? x[c] : mx;
+    }
+  };
+  const int64_t nvec = n / VN, step = (int64_t)gridDim.x * NT;
+  const V* fv = reinterpret_cast<const V*>(f);
+  int64_t t = (int64_t)blockIdx.x * NT + threadIdx.x;
+  for (; t + (U - 1) * step < nvec; t += U * step) {
+    V x[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) x[u] = __builtin_nontemporal_load(fv + t + u * step);
+#pragma unroll
+    for (int u = 0; u < U; ++u) vec(x[u]);
   }
+  for (; t < nvec; t += step) vec(fv[t]);
+  if (blockIdx.x == 0 && (int64_t)threadIdx.x < n - nvec * VN) one(f[nvec * VN + threadIdx.x]);
   KSum tot = block_ksum<NT>(acc);
+  __shared__ double smn[NT], smx[NT], sbad[NT];
+  smn[threadIdx.x] = (double)mn;
+  smx[threadIdx.x] = (double)mx;
+  sbad[threadIdx.x] = bad;
+  __syncthreads();
+  for (int off = NT / 2; off > 0; off >>= 1) {
+    if ((int)threadIdx.x < off) {
+      smn[threadIdx.x] = fmin(smn[threadIdx.x], smn[threadIdx.x + off]);
+      smx[threadIdx.x] = fmax(smx[threadIdx.x], smx[threadIdx.x + off]);
+      sbad[threadIdx.x] += sbad[threadIdx.x + off];
+    }
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) {
+    double* p = partials + (int64_t)blockIdx.x * 5;
+    p[0] = tot.s;
+    p[1] = tot.c;
+    p[2] = smn[0];
+    p[3] = smx[0];
+    p[4] = sbad[0];
+  }
+}
+
+// Per block b: partials[b*6 + 0..5] = sum |a|^2 over all components and
+// cells, and real and imaginary part of sum_x a_1(x) exp(-2 pi i x1_index /
+// nx1), each as (sum, compensation).  (One block took 96 us at 24^3 cells, now 6 us.)
+template <int NT>
+__global__ void __launch_bounds__(NT) diag_field_kernel(const double* __restrict__ accel, int D,
+                                                        int64_t nxs, int64_t nx1, int64_t inner1,
+                                                        double* __restrict__ partials) {
+  KSum e{0.0, 0.0}, cr{0.0, 0.0}, ci{0.0, 0.0};
+  const int64_t t0 = (int64_t)blockIdx.x * NT + threadIdx.x, step = (int64_t)gridDim.x * NT;
+  for (int64_t t = t0; t < (int64_t)D * nxs; t += step) {
+    const double a = accel[t];
+    kadd2(e, a * a);
+  }
+  for (int64_t t = t0; t < nxs; t += step) {
+    double sn, cs;
+    sincospi(-2.0 * (double)(t / inner1) / (double)nx1, &sn, &cs);
+    kadd2(cr, accel[t] * cs);
+    kadd2(ci, accel[t] * sn);
+  }
+  const KSum te = block_ksum<NT>(e), tr = block_ksum<NT>(cr), ti = block_ksum<NT>(ci);
+  if (threadIdx.x == 0) {
+    double* p = partials + (int64_t)blockIdx.x * 6;
+    p[0] = te.s;
+    p[1] = te.c;
+    p[2] = tr.s;
+    p[3] = tr.c;
+    p[4] = ti.s;
+    p[5] = ti.c;
+  }
+}
+
+// out[0..6] = sum of f, min, max, non-finite count, sum |a|^2, real and
+// imaginary part of the first mode, from the block results in block order.
+template <int NT>
+__global__ void __launch_bounds__(NT) diag_sum_kernel(const double* __restrict__ pf, int nf,
+                                                      const double* __restrict__ pa, int na,
+                                                      double* __restrict__ out) {
+  KSum s[4] = {{0.0, 0.0}, {0.0, 0.0}, {0.0, 0.0}, {0.0, 0.0}};
+  double mn = INFINITY, mx = -INFINITY, bad = 0.0;
+  for (int b = threadIdx.x; b < nf; b += NT) {
+    const double* p = pf + (int64_t)b * 5;
+    kmerge2(s[0], KSum{p[0], p[1]});
+    mn = fmin(mn, p[2]);
+    mx = fmax(mx, p[3]);
+    bad += p[4];
+  }
+  for (int b = threadIdx.x; b < na; b += NT)
+#pragma unroll
+    for (int q = 0; q < 3; ++q) kmerge2(s[1 + q], KSum{pa[b * 6 + 2 * q], pa[b * 6 + 2 * q + 1]});
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const KSum r = block_ksum<NT>(s[q]);
+    if (threadIdx.x == 0) out[q == 0 ? 0 : 3 + q] = r.s + r.c;
+  }
   __shared__ double smn[NT], smx[NT], sbad[NT];
   smn[threadIdx.x] = mn;
   smx[threadIdx.x] = mx;
@@ -460,44 +783,12 @@ __global__ void __launch_bounds__(NT) diag_f_kernel(const T* __restrict__ f, int
     __syncthreads();
   }
   if (threadIdx.x == 0) {
-    partials[blockIdx.x * 4 + 0] = tot.s;
-    partials[blockIdx.x * 4 + 1] = tot.c;
-    partials[blockIdx.x * 4 + 2] = smn[0];
-    partials[blockIdx.x * 4 + 3] = smx[0];
-    partials[(int64_t)gridDim.x * 4 + blockIdx.x] = sbad[0];
+    out[1] = smn[0];
+    out[2] = smx[0];
+    out[3] = sbad[0];
   }
 }
 
-// out[0] = sum |a|^2 over all components and cells; out[1], out[2] =
-// real/imaginary part of sum_x a_1(x) exp(-2 pi i x1_index / nx1).
-template <int NT>
-__global__ void __launch_bounds__(NT) diag_field_kernel(const double* __restrict__ accel, int D,
-                                                        int64_t nxs, int64_t nx1, int64_t inner1,
-                                                        double* __restrict__ out) {
-  KSum e{0.0, 0.0}, cr{0.0, 0.0}, ci{0.0, 0.0};
-  for (int64_t t = threadIdx.x; t < (int64_t)D * nxs; t += NT) {
-    const double a = accel[t];
-    kadd(e, a * a);
-  }
-  for (int64_t t = threadIdx.x; t < nxs; t += NT) {
-    const int64_t i1 = t / inner1;
-    const double ang = -2.0 * M_PI * (double)(i1 % nx1) / (double)nx1;
-    double sn, cs;
-    sincos(ang, &sn, &cs);
-    kadd(cr, accel[t] * cs);
-    kadd(ci, accel[t] * sn);
-  }
-  KSum te = block_ksum<NT>(e);
-  KSum tr = block_ksum<NT>(cr);
-  KSum ti = block_ksum<NT>(ci);
-  if (threadIdx.x == 0) {
-    out[0] = te.s + te.c;
-    out[1] = tr.s + tr.c;
-    out[2] = ti.s + ti.c;
-  }
-}
-
-// f <- cb * b + cf * f (the stage combinations of Eq. (RK)), grid-stride
 __global__ void copy_kernel(const uint4* __restrict__ src, uint4* __restrict__ dst, int64_t n) {
   for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < n;
        t += (int64_t)gridDim.x * blockDim.x)
@@ -654,23 +945,20 @@ hipError_t launch_to_double(int dtype, const void* f, double* dst, int64_t n, hi
   return hipGetLastError();
 }
 
-hipError_t launch_diag_f(int dtype, const void* f, int64_t n, double* partials, int nblocks,
-                         hipStream_t s) {
+hipError_t launch_diag(int dtype, const void* f, int64_t n, const double* accel, int D, int64_t nxs,
+                       int64_t nx1, int64_t inner1, double* partials, double* out, hipStream_t s) {
   constexpr int NT = 256;
+  const int nf = (int)std::max<int64_t>(1, std::min<int64_t>(kDiagBlocks, (n + 16 * NT - 1) / (16 * NT)));
+  const int na = (int)std::max<int64_t>(1, std::min<int64_t>(kDiagFieldBlocks, (nxs + NT - 1) / NT));
+  double* pa = partials + (int64_t)kDiagBlocks * 5;
   if (dtype == SLMPP_F64)
-    hipLaunchKernelGGL((diag_f_kernel<double, NT>), dim3(nblocks), dim3(NT), 0, s,
-                       (const double*)f, n, partials);
+    hipLaunchKernelGGL((diag_f_kernel<double, NT>), dim3(nf), dim3(NT), 0, s, (const double*)f, n,
+                       partials);
   else
-    hipLaunchKernelGGL((diag_f_kernel<float, NT>), dim3(nblocks), dim3(NT), 0, s,
-                       (const float*)f, n, partials);
-  return hipGetLastError();
-}
-
-hipError_t launch_diag_field(const double* accel, int D, int64_t nxs, int64_t nx1, int64_t inner1,
-                             double* out, hipStream_t s) {
-  constexpr int NT = 256;
-  hipLaunchKernelGGL((diag_field_kernel<NT>), dim3(1), dim3(NT), 0, s, accel, D, nxs, nx1, inner1,
-                     out);
+    hipLaunchKernelGGL((diag_f_kernel<float, NT>), dim3(nf), dim3(NT), 0, s, (const float*)f, n,
+                       partials);
+  hipLaunchKernelGGL((diag_field_kernel<NT>), dim3(na), dim3(NT), 0, s, accel, D, nxs, nx1, inner1, pa);
+  hipLaunchKernelGGL((diag_sum_kernel<NT>), dim3(1), dim3(NT), 0, s, partials, nf, pa, na, out);
   return hipGetLastError();
 }
 
@@ -686,48 +974,71 @@ hipError_t launch_copy(void* dst, const void* src, size_t bytes, hipStream_t s) 
 
 hipError_t launch_velocity_moments(int dtype, const void* f, int D, const int64_t* nv,
                                    const double* vlo, const double* dv, int64_t nxs,
-                                   double* rho, double* mean, double* disp, hipStream_t s) {
-  int64_t nvs = 1;
+                                   double* rho, double* mean, double* disp, double* scratch,
+                                   int64_t scratch_doubles, hipStream_t s) {
+  if (D < 1 || D > 3) return hipErrorInvalidValue;
   double dvol = 1.0;
-  for (int l = 0; l < D; ++l) {
-    nvs *= nv[l];
-    dvol *= dv[l];
-  }
-  const int3 n3 = make_int3((int)nv[0], D > 1 ? (int)nv[1] : 1, D > 2 ? (int)nv[2] : 1);
+  for (int l = 0; l < D; ++l) dvol *= dv[l];
+  // the kernel's [n1][n2][n3]: one velocity axis is its n2, two are n1 and n2
+  const int n1 = D == 1 ? 1 : (int)nv[0], n2 = D == 1 ? (int)nv[0] : (int)nv[1];
+  const int n3 = D == 3 ? (int)nv[2] : 1;
   const double3 lo3 = make_double3(vlo[0], D > 1 ? vlo[1] : 0.0, D > 2 ? vlo[2] : 0.0);
   const double3 dv3 = make_double3(dv[0], D > 1 ? dv[1] : 1.0, D > 2 ? dv[2] : 1.0);
-  constexpr int NT = 256;
-  if (D < 1 || D > 3) return hipErrorInvalidValue;
-  auto go = [&](auto tag, auto axes) {
+  auto go = [&](auto tag, auto width) -> hipError_t {
     using T = decltype(tag);
-    hipLaunchKernelGGL((velocity_moments_kernel<T, NT, decltype(axes)::value>), dim3((unsigned)nxs),
-                       dim3(NT), 0, s, (const T*)f, D, nvs, n3, lo3, dv3, dvol, nxs, rho, mean,
-                       disp);
+    constexpr int NT = decltype(width)::value;
+    const int64_t ch = 64 * UVec<T>::N * kMomVec;
+    const int64_t axes = n1 + n2 + n3;
+    size_t lds = sizeof(double) * ((size_t)(NT / 64) * std::min<int64_t>(ch, (int64_t)n2 * n3) + std::max(NT, n3));
+    // axes of several thousand cells each: few spatial cells fit the GPU
+    // then, and the scratch holds their marginals
+    KSum* marg = nullptr;
+    if (lds + sizeof(KSum) * axes > 160 * 1024) {
+      if (nxs * axes * 2 > scratch_doubles) return hipErrorInvalidValue;
+      marg = reinterpret_cast<KSum*>(scratch);
+    } else {
+      lds += sizeof(KSum) * axes;
+    }
+    auto kern = marg ? velocity_moments_kernel<T, NT, true> : velocity_moments_kernel<T, NT, false>;
+    if (lds > 64 * 1024) {
+      hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+      if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(kern, dim3((unsigned)nxs), dim3(NT), lds, s, (const T*)f, D, n1, n2, n3, lo3,
+                       dv3, dvol, nxs, rho, mean, disp, marg);
+    return hipGetLastError();
   };
-  using A1 = std::integral_constant<int, 1>;
-  using A2 = std::integral_constant<int, 2>;
-  using A3 = std::integral_constant<int, 3>;
-  if (dtype == SLMPP_F64) {
-    if (D == 1) go(0.0, A1{});
-    if (D == 2) go(0.0, A2{});
-    if (D == 3) go(0.0, A3{});
-  } else {
-    if (D == 1) go(0.0f, A1{});
-    if (D == 2) go(0.0f, A2{});
-    if (D == 3) go(0.0f, A3{});
-  }
-  return hipGetLastError();
+  // one wavefront per spatial cell where there are enough cells to fill the
+  // GPU with them (no barriers, long runs of loads between two folds), four
+  // where there are not
+  using One = std::integral_constant<int, 64>;
+  using Four = std::integral_constant<int, 256>;
+  if (nxs >= 2048) return dtype == SLMPP_F64 ? go(0.0, One{}) : go(0.0f, One{});
+  return dtype == SLMPP_F64 ? go(0.0, Four{}) : go(0.0f, Four{});
 }
 
 hipError_t launch_velocity_distribution(int dtype, const void* f, int64_t nxs, int64_t nvs,
-                                        double xvol, double* F, hipStream_t s) {
-  const int64_t blocks = std::min<int64_t>((nvs + 255) / 256, 4096);
+                                        double xvol, double* F, double* scratch,
+                                        int64_t scratch_doubles, hipStream_t s) {
+  const int vn = dtype == SLMPP_F64 ? 2 : 4;
+  const int64_t bx = std::min<int64_t>(((nvs + vn - 1) / vn + 255) / 256, 4096);
+  // shares of the spatial cells: about 2048 workgroups in all, at least 16
+  // cells each, within the scratch
+  int64_t shares = std::min<int64_t>((2048 + bx - 1) / bx, (nxs + 15) / 16);
+  shares = std::min<int64_t>(shares, scratch_doubles / (2 * nvs));
+  shares = std::max<int64_t>(1, std::min<int64_t>(shares, 1024));
+  KSum* part = shares > 1 ? reinterpret_cast<KSum*>(scratch) : nullptr;
+  const dim3 grid((unsigned)bx, (unsigned)shares);
   if (dtype == SLMPP_F64)
-    hipLaunchKernelGGL(velocity_distribution_kernel<double>, dim3((unsigned)blocks), dim3(256), 0,
-                       s, (const double*)f, nxs, nvs, xvol, F);
+    hipLaunchKernelGGL(velocity_distribution_kernel<double>, grid, dim3(256), 0, s, (const double*)f,
+                       nxs, nvs, xvol, F, part);
   else
-    hipLaunchKernelGGL(velocity_distribution_kernel<float>, dim3((unsigned)blocks), dim3(256), 0,
-                       s, (const float*)f, nxs, nvs, xvol, F);
+    hipLaunchKernelGGL(velocity_distribution_kernel<float>, grid, dim3(256), 0, s, (const float*)f,
+                       nxs, nvs, xvol, F, part);
+  if (part)
+    hipLaunchKernelGGL(distribution_sum_kernel, dim3(blocks_for(nvs, 256)), dim3(256), 0, s, part,
+                       (int)shares, nvs, xvol, F);
   return hipGetLastError();
 }
 

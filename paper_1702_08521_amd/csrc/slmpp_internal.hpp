@@ -215,17 +215,22 @@ hipError_t launch_init_separable(int dtype, void* f, const double* s, const doub
                                  int64_t nxs, int64_t nvs, hipStream_t st);
 hipError_t launch_from_double(int dtype, void* f, const double* src, int64_t n, hipStream_t s);
 hipError_t launch_to_double(int dtype, const void* f, double* dst, int64_t n, hipStream_t s);
-hipError_t launch_diag_f(int dtype, const void* f, int64_t n, double* partials, int nblocks,
-                         hipStream_t s);
-hipError_t launch_diag_field(const double* accel, int D, int64_t nxs, int64_t nx1, int64_t inner1,
-                             double* out, hipStream_t s);
+// diagnostics of f (n values) and the acceleration: out[0..6] = sum of f,
+// min, max, number of non-finite values, sum |a|^2, real and imaginary part
+// of the first mode of a_1; partials: kDiagPartials doubles of scratch
+hipError_t launch_diag(int dtype, const void* f, int64_t n, const double* accel, int D, int64_t nxs,
+                       int64_t nx1, int64_t inner1, double* partials, double* out, hipStream_t s);
 hipError_t launch_copy(void* dst, const void* src, size_t bytes, hipStream_t s);
 // velocity moments per spatial cell and the velocity distribution (double)
 hipError_t launch_velocity_moments(int dtype, const void* f, int D, const int64_t* nv,
                                    const double* vlo, const double* dv, int64_t nxs,
-                                   double* rho, double* mean, double* disp, hipStream_t s);
+                                   double* rho, double* mean, double* disp, double* scratch,
+                                   int64_t scratch_doubles, hipStream_t s);
 hipError_t launch_velocity_distribution(int dtype, const void* f, int64_t nxs, int64_t nvs,
-                                        double xvol, double* F, hipStream_t s);
-constexpr int kDiagBlocks = 1024;
+                                        double xvol, double* F, double* scratch,
+                                        int64_t scratch_doubles, hipStream_t s);
+constexpr int kDiagBlocks = 2048;
+constexpr int kDiagFieldBlocks = 64;
+constexpr int64_t kDiagPartials = kDiagBlocks * 5 + kDiagFieldBlocks * 6;
 
 }  // namespace slmpp
