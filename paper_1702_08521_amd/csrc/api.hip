@@ -197,6 +197,17 @@ SweepArgs v_sweep_args(const slmpp_grid_desc& d, const int64_t* dims, int l, dou
   s.nfast = 4;
   return s;
 }
+
+// Whether a sweep goes to line_sweep_kernel (when that takes it): sizes
+// without a compile-time tile, other limiters and TVD-RK; and instead of the
+// narrow tiles of sweep_fast_kernel, 48 pencils where the stride has room for
+// wider rows (18 x 20 x 24 x 30 x 36 x 42 FP32, x3 sweep: 861 -> 715 us; at a
+// stride of 48 both take the same time) and 32 pencils (36 x 36 x 24 x 16 x
+// 16 x 32 FP64, v2 sweep: 1362 -> 889 us).  The wider tiles of
+// sweep_fast_kernel are up to 30% faster than line_sweep_kernel.
+bool line_preferred(const SweepPlan& p, const SweepArgs& a) {
+  return !p.fast || a.rk || (a.inner > 1 && (p.W == 32 || (p.W == 48 && a.inner > 256)));
+}
 }  // namespace
 
 struct slmpp_ctx {
@@ -245,7 +256,7 @@ struct slmpp_ctx {
   bool small_field = false;
   void* rkbuf() { return work + lay.rkbuf; }
   bool rk = false;  // SLMPP_FLAG_RK3
-  int mom_w = 64;  // tile width of the last fused x_1 sweep
+  int64_t mom_sub = 1;  // tiles per velocity block of the last fused x_1 sweep
   size_t esize() const { return d.storage == SLMPP_F64 ? 8 : 4; }
 
   slmpp_status fail(slmpp_status code, const char* fmt, ...) {
@@ -357,10 +368,25 @@ struct slmpp_ctx {
                              fuse_moment && !rk && a == 0);
     if (p.lds_bytes > 160 * 1024)
       return fail(SLMPP_ERR_SHAPE, "pencil of %d cells does not fit the LDS tile", s.n);
-    if (fuse_moment && !rk && a == 0 && p.fast && p.W >= 64 && inner > 1 &&
+    LinePlan lp{};
+    if (line_preferred(p, s)) {
+      const bool rows = fuse_moment && !rk && a == 0 && nvs >= 64 && ncell >= ((int64_t)1 << 22);
+      if (rows) {
+        lp = plan_line(d.storage, d.order, s, nvs);
+        if (lp.lds_bytes && lp.tiles * (int64_t)s.n <= lay.mom_doubles) {
+          s.mom = mom();
+          mom_sub = lp.tpb;
+          if (fused) *fused = true;
+        } else {
+          lp = LinePlan{};
+        }
+      }
+      if (!lp.lds_bytes) lp = plan_line(d.storage, d.order, s, 0);
+    }
+    if (!lp.lds_bytes && fuse_moment && !rk && a == 0 && p.fast && p.W >= 64 && inner > 1 &&
         nvs % p.W == 0 && p.tiles * (int64_t)s.n <= lay.mom_doubles) {
       s.mom = mom();
-      mom_w = p.W;
+      mom_sub = nvs / p.W;
       if (fused) *fused = true;
     }
     const double cells = (double)ncell;
@@ -368,8 +394,12 @@ struct slmpp_ctx {
     hipError_t e = tic(5, 0.0, 0.0);
     if (e == hipSuccess) e = launch_pencil_table(d.storage, d.order, s, table(), tcount, stream);
     if (e == hipSuccess) e = toc();
-    const int cls = inner == 1 ? 1 : (s.mom ? 6 : (p.W >= 128 ? 0 : 4));
-    if (!rk) {
+    const int cls = inner == 1 ? 1 : (s.mom ? 6 : ((lp.lds_bytes ? lp.W : p.W) >= 128 ? 0 : 4));
+    if (lp.lds_bytes) {
+      if (e == hipSuccess) e = tic(cls, 2.0 * cells * esize(), (rk ? 3.0 : 1.0) * cells);
+      if (e == hipSuccess) e = launch_line_sweep(d.storage, d.order, d.limiter, s, lp, table(), stream);
+      if (e == hipSuccess) e = toc();
+    } else if (!rk) {
       if (e == hipSuccess) e = tic(cls, 2.0 * cells * esize(), cells);
       if (e == hipSuccess) e = launch_sweep(d.storage, d.order, d.limiter, s, p, table(), stream);
       if (e == hipSuccess) e = toc();
@@ -490,7 +520,7 @@ struct slmpp_ctx {
     double dvol = 1.0;
     for (int l = 0; l < D; ++l) dvol *= hv[l];
     const int n = (int)d.nx[0];
-    const int64_t ncol = nxs / n, nsub = nvs / mom_w;
+    const int64_t ncol = nxs / n, nsub = mom_sub;
     hipError_t e = tic(2, 8.0 * (double)ncol * nsub * n + 8.0 * nxs, 0.0);
     if (e == hipSuccess) e = launch_moment_reduce(mom(), n, ncol, nsub, dvol, rho(), stream);
     if (e == hipSuccess) e = toc();
@@ -876,7 +906,10 @@ slmpp_status slmpp_advect_v_noalloc(const slmpp_grid_desc* desc, void* f_dev, in
   hipError_t e = scratch_for_current_device(&table);
   const hipStream_t stream = static_cast<hipStream_t>(hip_stream);
   if (e == hipSuccess) e = launch_pencil_table(desc->storage, desc->order, s, table, nxs, stream);
-  if (e == hipSuccess) e = launch_sweep(desc->storage, desc->order, desc->limiter, s, p, table, stream);
+  const LinePlan lp = line_preferred(p, s) ? plan_line(desc->storage, desc->order, s, 0) : LinePlan{};
+  if (e == hipSuccess)
+    e = lp.lds_bytes ? launch_line_sweep(desc->storage, desc->order, desc->limiter, s, lp, table, stream)
+                     : launch_sweep(desc->storage, desc->order, desc->limiter, s, p, table, stream);
   if (e != hipSuccess) {
     g_error = std::string("advect_v_noalloc: ") + hipGetErrorString(e);
     return SLMPP_ERR_DEVICE;

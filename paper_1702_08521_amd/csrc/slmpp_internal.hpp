@@ -119,6 +119,31 @@ struct PlanePlan {
   FastDiv32 vdiv;      // plane -> spatial cell (plane / vouter) while planes < 2^32
   size_t lds_bytes;    // 0: the shape is not supported
 };
+// Tiling of a sweep by line_sweep_kernel (any pencil length up to 2048, any
+// stride, limiter and time integration).  A tile is W pencils of one block
+// of `blen` consecutive pencils (rows of W elements, `inner` apart), or, when
+// K > 0, K whole blocks of `inner` pencils each (contiguous in f).
+struct LinePlan {
+  int32_t W, K;        // pencils per row tile; blocks per tile (0: row tiles)
+  int32_t pw;          // pencils per tile
+  int32_t S, R;        // segments per pencil, cells per segment (at most 16)
+  int32_t G;           // ghost cells on both sides of a pencil in LDS
+  int32_t rs, bs;      // LDS elements between cells of a pencil, between blocks
+  int32_t threads;     // pw * S rounded up to whole wavefronts
+  int32_t lds_elems;
+  int32_t tpb;         // row tiles per block
+  int32_t blen;        // pencils of a block of row tiles
+  int64_t blocks;      // number of blocks
+  int64_t bstride;     // elements between blocks of row tiles
+  int64_t tiles;
+  FastDiv32 dtpb, dvdiv, dnvl, dxdiv;
+  size_t lds_bytes;    // 0: the sweep is not one this kernel takes
+};
+// moment_block > 0: row tiles within velocity blocks of that many pencils,
+// for the row sums of SweepArgs::mom (x_1 sweeps).
+LinePlan plan_line(int dtype, int order, const SweepArgs& a, int64_t moment_block);
+hipError_t launch_line_sweep(int dtype, int order, int limiter, const SweepArgs& a,
+                             const LinePlan& p, const void* table, hipStream_t s);
 PlanePlan plan_kick_plane(int dtype, int order, int32_t na, int32_t nb, int64_t planes,
                           int64_t vouter);
 hipError_t launch_kick_plane(int dtype, int order, const SweepArgs& a, const PlanePlan& p,
@@ -176,8 +201,6 @@ hipError_t launch_batch_sweeps(int dtype, const BatchSweep* sweeps, const BatchI
 int batch_sweep_blocks_per_cu(int dtype, size_t lds_bytes);
 SweepPlan plan_batch_sweep(int dtype, int order, int32_t n, int64_t npen, int64_t inner,
                            int32_t nfast, int W);
-hipError_t launch_generic_sweep(int dtype, int order, const SweepArgs& a, const SweepPlan& p,
-                                const void* table, hipStream_t s);
 hipError_t launch_batch_moment(int dtype, const BatchRun* runs, const int2* items, int nitems,
                                hipStream_t s);
 hipError_t launch_batch_poisson(const BatchRun* runs, int nruns, int max_nxs, hipStream_t s);
