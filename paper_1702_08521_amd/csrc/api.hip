@@ -20,6 +20,11 @@ namespace {
 
 constexpr int64_t kMaxAxis = 4096;               // LDS holds a whole pencil
 constexpr int64_t kMaxCells = (int64_t)1 << 40;  // 1.1e12 cells
+// row sums that every workgroup of the one-dimensional field solve adds up;
+// more are left to the moment over f (1024 cells by 256 tiles: 256 KB for
+// each of 64 workgroups)
+constexpr int64_t kConvRowSums = (int64_t)1 << 15;
+constexpr int64_t kSmallCells = (int64_t)1 << 19;  // grids that do not fill the GPU
 constexpr int64_t kStageChunk = (int64_t)1 << 22;  // doubles per host<->device chunk
 
 thread_local std::string g_error;
@@ -27,8 +32,9 @@ thread_local std::string g_error;
 size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 struct Layout {
-  size_t rho, phi, accel, green, bufA, bufB, tw, partials, diagfield, table, table2, stage, mom, rkbuf,
-      isoA, isoB, isoG, tw2, prun, total;
+  size_t rho, phi, accel, green, bufA, bufB, tw, partials, diagfield, stage, mom, rkbuf, isoA, isoB,
+      isoG, tw2, conv, total;
+  size_t xt[3], vt[3];  // pencil tables of the sweeps along x_l and v_l
   int64_t stage_doubles, mom_doubles;
 };
 
@@ -66,15 +72,16 @@ Layout layout_of(const slmpp_grid_desc& d) {
   L.tw = take(sizeof(double2) * sumnx);
   L.partials = take(sizeof(double) * kDiagPartials);
   L.diagfield = take(sizeof(double) * 8);
-  int64_t maxnv = 1;
-  for (int l = 0; l < d.D; ++l) maxnv = std::max<int64_t>(maxnv, d.nv[l]);
-  L.table = take(pencil_table_bytes(SLMPP_F64, std::max<int64_t>(maxnv, nxs)));
-  L.table2 = take(pencil_table_bytes(SLMPP_F64, nxs));  // second axis of a two-axis kick
+  for (int l = 0; l < d.D; ++l) {
+    L.xt[l] = take(pencil_table_bytes(SLMPP_F64, d.nv[l]));
+    L.vt[l] = take(pencil_table_bytes(SLMPP_F64, nxs));
+  }
   L.stage_doubles = std::max<int64_t>(std::min<int64_t>(kStageChunk, ncell), nxs + sumnv);
   L.stage = take(sizeof(double) * L.stage_doubles);
   // row sums of the x_1 sweep's tiles (fused velocity moment; 64 or 128
-  // pencils per tile)
-  L.mom_doubles = ncell / 64;
+  // pencils per tile; down to 4 in one dimension)
+  L.mom_doubles = d.D == 1 ? std::min<int64_t>(ncell, kConvRowSums)
+                           : std::max<int64_t>(ncell / 64, std::min<int64_t>(ncell / 8, (int64_t)1 << 20));
   L.mom = take(sizeof(double) * std::max<int64_t>(L.mom_doubles, 1));
   // TVD-RK time integration keeps f^n of a sweep
   L.rkbuf = take((d.flags & SLMPP_FLAG_RK3) ? (size_t)ncell * (d.storage == SLMPP_F64 ? 8 : 4) : 0);
@@ -86,8 +93,8 @@ Layout layout_of(const slmpp_grid_desc& d) {
   L.isoB = take(sizeof(double2) * ms);
   L.isoG = take(sizeof(double) * ms);
   L.tw2 = take(iso ? sizeof(double2) * 2 * sumnx : 0);
-  // small periodic grids: the field of the context in one workgroup
-  L.prun = take(sizeof(BatchRun));
+  // one dimension: the solve's convolution kernels
+  L.conv = take(d.D == 1 ? sizeof(double) * 2 * nxs : 0);
   L.total = off;
   return L;
 }
@@ -204,9 +211,11 @@ SweepArgs v_sweep_args(const slmpp_grid_desc& d, const int64_t* dims, int l, dou
 // wider rows (18 x 20 x 24 x 30 x 36 x 42 FP32, x3 sweep: 861 -> 715 us; at a
 // stride of 48 both take the same time) and 32 pencils (36 x 36 x 24 x 16 x
 // 16 x 32 FP64, v2 sweep: 1362 -> 889 us).  The wider tiles of
-// sweep_fast_kernel are up to 30% faster than line_sweep_kernel.
+// sweep_fast_kernel are up to 30% faster than line_sweep_kernel, except on
+// grids too small to fill the GPU with them (64 x 48 FP64 step 31.3 -> 28.4
+// us, 16^2 x 32^2 FP64 52.3 -> 50.0 us; from half a million cells on equal).
 bool line_preferred(const SweepPlan& p, const SweepArgs& a) {
-  return !p.fast || a.rk || (a.inner > 1 && (p.W == 32 || (p.W == 48 && a.inner > 256)));
+  return !p.fast || a.rk || a.npen * a.n < kSmallCells || (a.inner > 1 && (p.W == 32 || (p.W == 48 && a.inner > 256)));
 }
 }  // namespace
 
@@ -242,8 +251,12 @@ struct slmpp_ctx {
   double* partials() { return reinterpret_cast<double*>(work + lay.partials); }
   double* diagfield() { return reinterpret_cast<double*>(work + lay.diagfield); }
   double* stage() { return reinterpret_cast<double*>(work + lay.stage); }
-  void* table() { return work + lay.table; }
-  void* table2() { return work + lay.table2; }
+  // pencil table of the sweeps along array axis a
+  void* table(int a) { return work + (a < D ? lay.xt[a] : lay.vt[a - D]); }
+  int64_t table_count(int a) const { return a < D ? d.nv[a] : nxs; }
+  double* conv() { return reinterpret_cast<double*>(work + lay.conv); }
+  FieldPlan fplan{};       // the four-launch field solve; ok 0: not a size it takes
+  bool conv_field = false; // the one-dimensional solve
   double* mom() { return reinterpret_cast<double*>(work + lay.mom); }
   double2* isoA() { return reinterpret_cast<double2*>(work + lay.isoA); }
   double2* isoB() { return reinterpret_cast<double2*>(work + lay.isoB); }
@@ -251,9 +264,6 @@ struct slmpp_ctx {
   double2* tw2() { return reinterpret_cast<double2*>(work + lay.tw2); }
   int64_t tw2_off[3]{};
   bool isolated = false;  // SLMPP_FLAG_ISOLATED
-  // periodic grid of at most kBatchMaxSpace cells: the context's own field
-  // solve runs as one workgroup in LDS (the batched ensembles' kernel)
-  bool small_field = false;
   void* rkbuf() { return work + lay.rkbuf; }
   bool rk = false;  // SLMPP_FLAG_RK3
   int64_t mom_sub = 1;  // tiles per velocity block of the last fused x_1 sweep
@@ -322,30 +332,24 @@ struct slmpp_ctx {
   }
 
   // --- one sweep along array axis a ---
-  // fuse_moment (x_1 sweeps only): when the sweep runs as strided 64-pencil
-  // tiles lying within velocity blocks, it also leaves per-tile row sums for
-  // the velocity moment and *fused is set.
-  slmpp_status sweep(int a, double dt, const double* accel_dev, bool fuse_moment = false,
-                     bool* fused = nullptr) {
-    if (fused) *fused = false;
+  SweepArgs sweep_args(int a, double dt, const double* accel_dev) {
     const int nd = 2 * D;
     int64_t inner = 1;
-    for (int k = a + 1; k < nd; ++k) inner *= dims[k];
-    int64_t outer = 1;
-    for (int k = 0; k < a; ++k) outer *= dims[k];
     SweepArgs s{};
-    s.f = f;
-    s.npen = outer * inner;
-    s.inner = inner;
-    s.n = (int32_t)dims[a];
-    s.dt = dt;
-    s.alpha = d.alpha;
     if (a >= D) {  // v_l sweep, speed a_l(x)
       s = v_sweep_args(d, dims, a - D, dt, accel_dev, f, inner);
     } else {  // x_l sweep, speed v_l
       const int l = a;
-      int64_t vdiv = 1;
+      for (int k = a + 1; k < nd; ++k) inner *= dims[k];
+      int64_t outer = 1, vdiv = 1;
+      for (int k = 0; k < a; ++k) outer *= dims[k];
       for (int k = D + l + 1; k < nd; ++k) vdiv *= dims[k];
+      s.f = f;
+      s.npen = outer * inner;
+      s.inner = inner;
+      s.n = (int32_t)dims[a];
+      s.dt = dt;
+      s.alpha = d.alpha;
       s.cmode = SPEED_FROM_VELOCITY;
       s.vdiv = vdiv;
       s.nvl = (int32_t)d.nv[l];
@@ -355,23 +359,60 @@ struct slmpp_ctx {
       s.bc = d.x_bc;
       s.xdiv = 1;
       s.nfast = max_shift_velocity(s.vlo, s.dv, s.nvl, dt, s.h, s.n, s.bc);
-      if (rk) {
-        slmpp_status st = check_rk_x(l, dt);
-        if (st != SLMPP_OK) return st;
-      }
     }
     if (rk) {
       s.rk = 1;
       s.nfast = 0;  // no integer shift in an RK stage
     }
+    return s;
+  }
+
+  // The pencil tables of the sweeps along the listed axes, in one launch.
+  slmpp_status make_tables(const TableJobs& jobs) {
+    if (jobs.n == 0) return SLMPP_OK;
+    hipError_t e = tic(5, 0.0, 0.0);
+    if (e == hipSuccess) e = launch_tables(d.storage, d.order, jobs, stream);
+    if (e == hipSuccess) e = toc();
+    return e == hipSuccess ? SLMPP_OK : hip_fail(e, "pencil table launch");
+  }
+  void add_v_tables(TableJobs& jobs, double dt) {
+    for (int l = 0; l < D; ++l)
+      jobs.add(sweep_args(D + l, dt, accel() + (int64_t)l * nxs), table(D + l), nxs);
+  }
+  // what the field solve needs to leave those tables
+  FieldTables v_tables(double dt) {
+    FieldTables t{};
+    for (int l = 0; l < D; ++l) {
+      t.tab[l] = table(D + l);
+      t.h[l] = hv[l];
+      t.n[l] = (int32_t)d.nv[l];
+    }
+    t.bc = d.v_bc;
+    t.rk = rk ? 1 : 0;
+    t.dt = dt;
+    return t;
+  }
+
+  // The sweep s along array axis a; its table has been made.  fuse_moment
+  // (x_1 sweeps only): when its tiles lie within velocity blocks, the sweep
+  // also leaves per-tile row sums for the velocity moment and *fused is set.
+  // reps > 1: that many sweeps one after the other, where the tile can take
+  // them while in LDS (*done: how many it did).
+  slmpp_status sweep(int a, SweepArgs s, bool fuse_moment = false, bool* fused = nullptr, int reps = 1,
+                     int* done = nullptr) {
+    if (fused) *fused = false;
+    if (done) *done = 1;
+    const int64_t inner = s.inner;
     SweepPlan p = plan_sweep(d.storage, d.order, d.limiter, s.n, s.npen, inner, s.nfast, 0, 0,
                              fuse_moment && !rk && a == 0);
     if (p.lds_bytes > 160 * 1024)
       return fail(SLMPP_ERR_SHAPE, "pencil of %d cells does not fit the LDS tile", s.n);
     LinePlan lp{};
     if (line_preferred(p, s)) {
-      const bool rows = fuse_moment && !rk && a == 0 && nvs >= 64 && ncell >= ((int64_t)1 << 22);
-      if (rows) {
+      // (row sums save a pass over f; in one dimension, where the solve adds
+      // them up itself, a launch)
+      if (fuse_moment && !rk && a == 0 &&
+          (D == 1 ? conv_field : nvs >= 64)) {
         lp = plan_line(d.storage, d.order, s, nvs);
         if (lp.lds_bytes && lp.tiles * (int64_t)s.n <= lay.mom_doubles) {
           s.mom = mom();
@@ -389,26 +430,27 @@ struct slmpp_ctx {
       mom_sub = nvs / p.W;
       if (fused) *fused = true;
     }
+    if (lp.lds_bytes && lp.K > 0 && !rk && reps > 1) {
+      lp.reps = reps;
+      if (done) *done = reps;
+    }
     const double cells = (double)ncell;
-    const int64_t tcount = a < D ? d.nv[a] : nxs;
-    hipError_t e = tic(5, 0.0, 0.0);
-    if (e == hipSuccess) e = launch_pencil_table(d.storage, d.order, s, table(), tcount, stream);
-    if (e == hipSuccess) e = toc();
     const int cls = inner == 1 ? 1 : (s.mom ? 6 : ((lp.lds_bytes ? lp.W : p.W) >= 128 ? 0 : 4));
+    hipError_t e = hipSuccess;
     if (lp.lds_bytes) {
-      if (e == hipSuccess) e = tic(cls, 2.0 * cells * esize(), (rk ? 3.0 : 1.0) * cells);
-      if (e == hipSuccess) e = launch_line_sweep(d.storage, d.order, d.limiter, s, lp, table(), stream);
+      e = tic(cls, 2.0 * cells * esize(), (rk ? 3.0 : (double)lp.reps) * cells);
+      if (e == hipSuccess) e = launch_line_sweep(d.storage, d.order, d.limiter, s, lp, table(a), stream);
       if (e == hipSuccess) e = toc();
     } else if (!rk) {
-      if (e == hipSuccess) e = tic(cls, 2.0 * cells * esize(), cells);
-      if (e == hipSuccess) e = launch_sweep(d.storage, d.order, d.limiter, s, p, table(), stream);
+      e = tic(cls, 2.0 * cells * esize(), cells);
+      if (e == hipSuccess) e = launch_sweep(d.storage, d.order, d.limiter, s, p, table(a), stream);
       if (e == hipSuccess) e = toc();
     } else {
       // Eq. (RK): f1 = S(f), f2 = 3/4 f + 1/4 S(f1), f^{n+1} = 1/3 f + 2/3 S(f2),
       // S(u) = u - nu L(u) one stage sweep.  The stages run out of place
       // with the combinations in their stores, f^n staying in f: f1 and f2
       // in rkbuf, the last stage back into f (8 passes over f per sweep)
-      if (e == hipSuccess) e = tic(cls, 8.0 * cells * esize(), 3.0 * cells);
+      e = tic(cls, 8.0 * cells * esize(), 3.0 * cells);
       SweepArgs s1 = s, s2 = s, s3 = s;
       s1.fout = rkbuf();
       s2.f = rkbuf();
@@ -420,9 +462,9 @@ struct slmpp_ctx {
       s3.fblend = f;
       s3.cb = 1.0 / 3.0;
       s3.cf = 2.0 / 3.0;
-      if (e == hipSuccess) e = launch_sweep(d.storage, d.order, d.limiter, s1, p, table(), stream);
-      if (e == hipSuccess) e = launch_sweep(d.storage, d.order, d.limiter, s2, p, table(), stream);
-      if (e == hipSuccess) e = launch_sweep(d.storage, d.order, d.limiter, s3, p, table(), stream);
+      if (e == hipSuccess) e = launch_sweep(d.storage, d.order, d.limiter, s1, p, table(a), stream);
+      if (e == hipSuccess) e = launch_sweep(d.storage, d.order, d.limiter, s2, p, table(a), stream);
+      if (e == hipSuccess) e = launch_sweep(d.storage, d.order, d.limiter, s3, p, table(a), stream);
       if (e == hipSuccess) e = toc();
     }
     if (e != hipSuccess) return hip_fail(e, "sweep launch");
@@ -442,41 +484,32 @@ struct slmpp_ctx {
   }
 
   // The velocity sweeps of one kick, v_1 .. v_D in that order with the
-  // current acceleration; v_{D-1} and v_D in one pass when possible.
-  slmpp_status kick(double dt) {
+  // current acceleration, whose tables for dt have been made; v_{D-1} and v_D
+  // in one pass when possible.  kicks: that many kicks one after the other.
+  slmpp_status kick(double dt, int kicks = 1) {
     const PlanePlan pp = kick_plane_plan();
     const int nsep = pp.lds_bytes ? D - 2 : D;
     slmpp_status st = SLMPP_OK;
-    for (int l = 0; l < nsep && st == SLMPP_OK; ++l) st = sweep(D + l, dt, accel() + (int64_t)l * nxs);
-    if (st != SLMPP_OK || nsep == D) return st;
-    SweepArgs sa[2];
-    for (int k = 0; k < 2; ++k) {
-      const int l = D - 2 + k;
-      SweepArgs& s = sa[k];
-      s = SweepArgs{};
-      s.f = f;
-      s.n = (int32_t)d.nv[l];
-      s.dt = dt;
-      s.alpha = d.alpha;
-      s.cmode = SPEED_FROM_ACCEL;
-      s.accel = accel() + (int64_t)l * nxs;
-      s.xdiv = 1;
-      s.vdiv = 1;
-      s.nvl = 1;
-      s.h = hv[l];
-      s.bc = d.v_bc;
-      s.nfast = 4;
+    for (int left = kicks; left > 0 && st == SLMPP_OK;) {
+      int done = 1;
+      for (int l = 0; l < nsep && st == SLMPP_OK; ++l)
+        st = sweep(D + l, sweep_args(D + l, dt, accel() + (int64_t)l * nxs), false, nullptr,
+                   D == 1 ? left : 1, &done);
+      if (st == SLMPP_OK && nsep < D) {
+        SweepArgs s{};
+        s.f = f;
+        s.alpha = d.alpha;
+        s.nfast = 4;
+        const double cells = (double)ncell;
+        hipError_t e = tic(7, 2.0 * cells * esize(), 2.0 * cells);
+        if (e == hipSuccess)
+          e = launch_kick_plane(d.storage, d.order, s, pp, table(2 * D - 2), table(2 * D - 1), stream);
+        if (e == hipSuccess) e = toc();
+        if (e != hipSuccess) st = hip_fail(e, "kick launch");
+      }
+      left -= done;
     }
-    const double cells = (double)ncell;
-    hipError_t e = tic(5, 0.0, 0.0);
-    if (e == hipSuccess) e = launch_pencil_table(d.storage, d.order, sa[0], table(), nxs, stream);
-    if (e == hipSuccess) e = launch_pencil_table(d.storage, d.order, sa[1], table2(), nxs, stream);
-    if (e == hipSuccess) e = toc();
-    if (e == hipSuccess) e = tic(7, 2.0 * cells * esize(), 2.0 * cells);
-    if (e == hipSuccess) e = launch_kick_plane(d.storage, d.order, sa[0], pp, table(), table2(), stream);
-    if (e == hipSuccess) e = toc();
-    if (e != hipSuccess) return hip_fail(e, "kick launch");
-    return SLMPP_OK;
+    return st;
   }
 
   slmpp_status moment(double* rho_dev) {
@@ -489,52 +522,92 @@ struct slmpp_ctx {
     return SLMPP_OK;
   }
 
-  slmpp_status poisson(const double* rho_dev, double* phi_dev, double* accel_dev) {
-    hipError_t e = tic(3, 8.0 * nxs * (2 + D), 0.0);
-    const bool own = rho_dev == rho() && (!phi_dev || phi_dev == phi()) && accel_dev == accel();
-    if (e == hipSuccess && small_field && own)
-      e = launch_batch_poisson(reinterpret_cast<const BatchRun*>(work + lay.prun), 1, (int)nxs, stream);
-    else if (e == hipSuccess && isolated)
-      e = launch_poisson_isolated(rho_dev, phi_dev ? phi_dev : phi(), accel_dev, isoA(), isoB(),
-                                  tw2(), tw2_off, isoG(), d.nx, hx, d.poisson_order, stream);
+  // phi and accel from the density rho_dev, or from the row sums `part` of an
+  // x_1 sweep (mom_sub per velocity block; rho_dev is written then).  tabs:
+  // the tables of the next velocity kick, left as well (with_tables: whether
+  // that was done; the caller makes them otherwise).
+  slmpp_status poisson(double* rho_dev, double* phi_dev, double* accel_dev, const double* part = nullptr,
+                       const FieldTables& tabs = FieldTables{}, bool* with_tables = nullptr) {
+    double dvol = 1.0;
+    for (int l = 0; l < D; ++l) dvol *= hv[l];
+    if (!phi_dev) phi_dev = phi();
+    if (with_tables) *with_tables = conv_field || fplan.ok;
+    const double solve_bytes = 8.0 * nxs * (2 + D);
+    const double part_bytes = 8.0 * (double)(nxs / d.nx[0]) * mom_sub * d.nx[0] + 8.0 * nxs;
+    hipError_t e = hipSuccess;
+    if (conv_field) {
+      // one launch; with row sums it is the moment's
+      e = part ? tic(2, part_bytes, 0.0) : tic(3, solve_bytes, 0.0);
+      if (e == hipSuccess)
+        e = launch_field_conv((int)nxs, part, (int)mom_sub, dvol, rho_dev, phi_dev, accel_dev, conv(),
+                              d.storage, d.order, tabs, stream);
+      if (e == hipSuccess) e = toc();
+      return e == hipSuccess ? SLMPP_OK : hip_fail(e, "field launch");
+    }
+    if (fplan.ok) {
+      double2* A = isolated ? isoA() : bufA();
+      double2* B = isolated ? isoB() : bufB();
+      const double2* t = isolated ? tw2() : tw();
+      if (part) e = tic(2, part_bytes, 0.0);
+      else e = tic(3, solve_bytes, 0.0);
+      if (e == hipSuccess) e = launch_field_forward(fplan, part, (int)mom_sub, dvol, rho_dev, A, t, stream);
+      if (part && e == hipSuccess) e = toc();
+      if (part && e == hipSuccess) e = tic(3, solve_bytes, 0.0);
+      if (e == hipSuccess)
+        e = launch_field_rest(fplan, phi_dev, accel_dev, A, B, reinterpret_cast<double*>(A), t,
+                              isolated ? isoG() : green(), d.storage, d.order, tabs, stream);
+      if (e == hipSuccess) e = toc();
+      return e == hipSuccess ? SLMPP_OK : hip_fail(e, "field launch");
+    }
+    if (part) {
+      const int n = (int)d.nx[0];
+      e = tic(2, part_bytes, 0.0);
+      if (e == hipSuccess) e = launch_moment_reduce(part, n, nxs / n, mom_sub, dvol, rho_dev, stream);
+      if (e == hipSuccess) e = toc();
+    }
+    if (e == hipSuccess) e = tic(3, solve_bytes, 0.0);
+    if (e == hipSuccess && isolated)
+      e = launch_poisson_isolated(rho_dev, phi_dev, accel_dev, isoA(), isoB(), tw2(), tw2_off, isoG(), d.nx,
+                                  hx, d.poisson_order, stream);
     else if (e == hipSuccess)
-      e = launch_poisson(rho_dev, phi_dev ? phi_dev : phi(), accel_dev, bufA(), bufB(), tw(),
-                         tw_off, green(), D, d.nx, hx, d.poisson_order, stream);
+      e = launch_poisson(rho_dev, phi_dev, accel_dev, bufA(), bufB(), tw(), tw_off, green(), D, d.nx, hx,
+                         d.poisson_order, stream);
     if (e == hipSuccess) e = toc();
     if (e != hipSuccess) return hip_fail(e, "poisson launch");
     return SLMPP_OK;
   }
 
-  // one Strang step with the current field: kick, x sweeps, field, kick
-  slmpp_status step_body(double dt) {
-    slmpp_status st = kick(0.5 * dt);
-    bool fused = false;
-    for (int l = D - 1; l >= 0 && st == SLMPP_OK; --l) st = sweep(l, dt, nullptr, l == 0, &fused);
-    if (st == SLMPP_OK) st = fused ? field_from_rowsums() : field();
-    if (st == SLMPP_OK) st = kick(0.5 * dt);
-    return st;
-  }
-
-  // the field after an x_1 sweep that left its tile row sums (see sweep)
-  slmpp_status field_from_rowsums() {
-    double dvol = 1.0;
-    for (int l = 0; l < D; ++l) dvol *= hv[l];
-    const int n = (int)d.nx[0];
-    const int64_t ncol = nxs / n, nsub = mom_sub;
-    hipError_t e = tic(2, 8.0 * (double)ncol * nsub * n + 8.0 * nxs, 0.0);
-    if (e == hipSuccess) e = launch_moment_reduce(mom(), n, ncol, nsub, dvol, rho(), stream);
-    if (e == hipSuccess) e = toc();
-    if (e != hipSuccess) return hip_fail(e, "moment reduce launch");
-    slmpp_status st = poisson(rho(), phi(), accel());
+  // The context's field (from the row sums of the x_1 sweep just done, or
+  // from f) and the tables of a kick by kick_dt with it (0: none).
+  slmpp_status field(double kick_dt = 0.0, bool rowsums = false) {
+    slmpp_status st = rowsums ? SLMPP_OK : moment(rho());
+    bool with_tables = false;
+    const FieldTables tabs = kick_dt != 0.0 ? v_tables(kick_dt) : FieldTables{};
+    if (st == SLMPP_OK)
+      st = poisson(rho(), phi(), accel(), rowsums ? mom() : nullptr, tabs, &with_tables);
+    if (st == SLMPP_OK && kick_dt != 0.0 && !with_tables) {
+      TableJobs jobs{};
+      add_v_tables(jobs, kick_dt);
+      st = make_tables(jobs);
+    }
     if (st == SLMPP_OK) field_valid = true;
     return st;
   }
 
-  slmpp_status field() {
-    slmpp_status st = moment(rho());
-    if (st == SLMPP_OK) st = poisson(rho(), phi(), accel());
-    if (st == SLMPP_OK) field_valid = true;
-    return st;
+  // field, if f changed since the last one, and the tables of a kick by
+  // kick_dt; with x_dt != 0 those of the x sweeps too
+  slmpp_status prepare(double kick_dt, double x_dt) {
+    TableJobs jobs{};
+    if (x_dt != 0.0)
+      for (int l = 0; l < D; ++l) jobs.add(sweep_args(l, x_dt, nullptr), table(l), d.nv[l]);
+    slmpp_status st = SLMPP_OK;
+    if (!field_valid) {
+      st = field(kick_dt);
+      if (kick_dt == 0.0) add_v_tables(jobs, kick_dt);
+    } else {
+      add_v_tables(jobs, kick_dt);
+    }
+    return st == SLMPP_OK ? make_tables(jobs) : st;
   }
 };
 
@@ -742,26 +815,11 @@ slmpp_status slmpp_create(const slmpp_grid_desc* desc, void* f_dev, void* work_d
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
     c->isolated = (desc->flags & SLMPP_FLAG_ISOLATED) != 0;
     if (e == hipSuccess && c->isolated) e = iso_setup(c, *desc);
-    if (e == hipSuccess && !c->isolated && c->nxs <= kBatchMaxSpace) {
-      BatchRun R{};
-      R.f = c->f;
-      R.rho = c->rho();
-      R.phi = c->phi();
-      R.accel = c->accel();
-      R.nxs = c->nxs;
-      R.nvs = c->nvs;
-      R.dvol = 1.0;
-      for (int l = 0; l < 3; ++l) {
-        R.nx[l] = l < c->D ? desc->nx[l] : 1;
-        R.h[l] = l < c->D ? c->hx[l] : 1.0;
-      }
-      R.kappa = desc->kappa;
-      R.D = c->D;
-      R.poisson_order = desc->poisson_order;
-      e = hipMemcpyAsync(c->work + c->lay.prun, &R, sizeof(R), hipMemcpyHostToDevice, c->stream);
-      if (e == hipSuccess) e = prepare_batch_kernels(desc->storage, 0, (int)c->nxs);
-      if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-      c->small_field = e == hipSuccess;
+    c->fplan = plan_field(c->D, desc->nx, c->hx, desc->poisson_order, c->isolated);
+    c->conv_field = c->D == 1 && c->nxs <= kConvMax;
+    if (e == hipSuccess && c->conv_field) {
+      e = launch_conv_setup((int)c->nxs, c->hx[0], desc->poisson_order, c->green(), c->tw(), c->conv(),
+                            c->stream);
     }
     if (e != hipSuccess) {
       g_error = std::string("upload of field tables: ") + hipGetErrorString(e);
@@ -838,7 +896,15 @@ slmpp_status slmpp_advect_x(slmpp_ctx* c, int32_t dim, double dt) {
   if (!std::isfinite(dt)) return c->fail(SLMPP_ERR_NONFINITE, "dt is not finite");
   c->field_valid = false;
   if (dt == 0.0) return SLMPP_OK;
-  return c->sweep(dim, dt, nullptr);
+  if (c->rk) {
+    slmpp_status st = c->check_rk_x(dim, dt);
+    if (st != SLMPP_OK) return st;
+  }
+  const SweepArgs s = c->sweep_args(dim, dt, nullptr);
+  TableJobs jobs{};
+  jobs.add(s, c->table(dim), c->table_count(dim));
+  slmpp_status st = c->make_tables(jobs);
+  return st == SLMPP_OK ? c->sweep(dim, s) : st;
 }
 
 slmpp_status slmpp_advect_v(slmpp_ctx* c, int32_t dim, double dt, const double* accel_dev) {
@@ -848,7 +914,12 @@ slmpp_status slmpp_advect_v(slmpp_ctx* c, int32_t dim, double dt, const double* 
   if (!accel_dev) return c->fail(SLMPP_ERR_INVALID, "accel_dev is NULL");
   c->field_valid = false;
   if (dt == 0.0) return SLMPP_OK;
-  return c->sweep(c->D + dim, dt, accel_dev);
+  const int a = c->D + dim;
+  const SweepArgs s = c->sweep_args(a, dt, accel_dev);
+  TableJobs jobs{};
+  jobs.add(s, c->table(a), c->table_count(a));
+  slmpp_status st = c->make_tables(jobs);
+  return st == SLMPP_OK ? c->sweep(a, s) : st;
 }
 
 slmpp_status slmpp_advect_v_noalloc(const slmpp_grid_desc* desc, void* f_dev, int32_t dim,
@@ -905,7 +976,9 @@ slmpp_status slmpp_advect_v_noalloc(const slmpp_grid_desc* desc, void* f_dev, in
   void* table = nullptr;
   hipError_t e = scratch_for_current_device(&table);
   const hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-  if (e == hipSuccess) e = launch_pencil_table(desc->storage, desc->order, s, table, nxs, stream);
+  TableJobs jobs{};
+  jobs.add(s, table, nxs);
+  if (e == hipSuccess) e = launch_tables(desc->storage, desc->order, jobs, stream);
   const LinePlan lp = line_preferred(p, s) ? plan_line(desc->storage, desc->order, s, 0) : LinePlan{};
   if (e == hipSuccess)
     e = lp.lds_bytes ? launch_line_sweep(desc->storage, desc->order, desc->limiter, s, lp, table, stream)
@@ -920,9 +993,9 @@ slmpp_status slmpp_advect_v_noalloc(const slmpp_grid_desc* desc, void* f_dev, in
 slmpp_status slmpp_kick(slmpp_ctx* c, double dt) {
   if (!c) return SLMPP_ERR_INVALID;
   if (!std::isfinite(dt)) return c->fail(SLMPP_ERR_NONFINITE, "dt is not finite");
-  slmpp_status st = SLMPP_OK;
-  if (!c->field_valid) st = c->field();
-  if (st != SLMPP_OK || dt == 0.0) return st;
+  if (dt == 0.0) return c->field_valid ? SLMPP_OK : c->field();
+  slmpp_status st = c->prepare(dt, 0.0);
+  if (st != SLMPP_OK) return st;
   c->field_valid = false;
   return c->kick(dt);
 }
@@ -960,7 +1033,7 @@ slmpp_status slmpp_poisson_solve(slmpp_ctx* c, const double* rho_dev, double* ph
                                  double* accel_dev) {
   if (!c) return SLMPP_ERR_INVALID;
   if (!rho_dev || !accel_dev) return c->fail(SLMPP_ERR_INVALID, "rho_dev and accel_dev must be non-NULL");
-  return c->poisson(rho_dev, phi_dev, accel_dev);
+  return c->poisson(const_cast<double*>(rho_dev), phi_dev, accel_dev);
 }
 
 slmpp_status slmpp_field(slmpp_ctx* c) {
@@ -1002,31 +1075,26 @@ slmpp_status slmpp_step(slmpp_ctx* c, double dt, int32_t nsteps) {
       if (st != SLMPP_OK) return st;
     }
   }
-  if (c->d.flags & SLMPP_FLAG_MERGE_KICKS) {
-    // v(dt/2) [x block, field, v(dt)]... ending with v(dt/2)
-    slmpp_status st = SLMPP_OK;
-    if (!c->field_valid) st = c->field();
-    if (st == SLMPP_OK) st = c->kick(0.5 * dt);
-    for (int32_t it = 0; it < nsteps && st == SLMPP_OK; ++it) {
-      bool fused = false;
-      for (int l = D - 1; l >= 0 && st == SLMPP_OK; --l)
-        st = c->sweep(l, dt, nullptr, l == 0, &fused);
-      if (st == SLMPP_OK) st = fused ? c->field_from_rowsums() : c->field();
-      if (st == SLMPP_OK) st = c->kick(it + 1 < nsteps ? dt : 0.5 * dt);
-    }
-    if (st != SLMPP_OK) c->field_valid = false;
-    return st;
+  // v(dt/2), then per step x block, field, v(dt/2), and between steps the
+  // opening v(dt/2) of the next: in one sweep of the tiles with the closing
+  // one where the kernel can (one dimension), or merged into one v(dt)
+  const bool merged = (c->d.flags & SLMPP_FLAG_MERGE_KICKS) != 0;
+  const double half = 0.5 * dt;
+  slmpp_status st = SLMPP_OK;
+  if (dt == 0.0) return c->field();  // nothing moves; a step ends with the field of f
+  st = c->prepare(half, dt);
+  if (st == SLMPP_OK) st = c->kick(half);
+  for (int32_t it = 0; it < nsteps && st == SLMPP_OK; ++it) {
+    bool fused = false;
+    const bool last = it + 1 == nsteps;
+    for (int l = D - 1; l >= 0 && st == SLMPP_OK; --l)
+      st = c->sweep(l, c->sweep_args(l, dt, nullptr), l == 0, &fused);
+    const double next = merged && !last ? dt : half;
+    if (st == SLMPP_OK) st = c->field(next, fused);
+    if (st == SLMPP_OK) st = c->kick(next, merged || last ? 1 : 2);
   }
-  for (int32_t it = 0; it < nsteps; ++it) {
-    slmpp_status st = SLMPP_OK;
-    if (!c->field_valid) st = c->field();
-    if (st == SLMPP_OK) st = c->step_body(dt);
-    if (st != SLMPP_OK) {
-      c->field_valid = false;
-      return st;
-    }
-  }
-  return SLMPP_OK;
+  if (st != SLMPP_OK) c->field_valid = false;
+  return st;
 }
 
 slmpp_status slmpp_get_f(slmpp_ctx* c, double* f_host, int64_t n) {

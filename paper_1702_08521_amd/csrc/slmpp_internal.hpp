@@ -69,10 +69,20 @@ struct SweepPlan {
 SweepPlan plan_sweep(int dtype, int order, int limiter, int32_t n, int64_t npen, int64_t inner,
                      int32_t nfast, int W_override = 0, int S_override = 0, bool moment = false);
 
-// Enqueue the pencil table (table_count entries, one per distinct speed;
-// `table` is device scratch of pencil_table_bytes()), then the sweep.
-hipError_t launch_pencil_table(int dtype, int order, const SweepArgs& a, void* table,
-                               int64_t table_count, hipStream_t s);
+// Pencil tables of up to six sweeps (count entries each, one per distinct
+// speed; tab: device scratch of pencil_table_bytes()).
+struct TableJobs {
+  SweepArgs a[6];
+  void* tab[6];
+  int32_t count[6];
+  int32_t n;
+  void add(const SweepArgs& s, void* t, int64_t c) {
+    a[n] = s;
+    tab[n] = t;
+    count[n++] = (int32_t)c;
+  }
+};
+hipError_t launch_tables(int dtype, int order, const TableJobs& jobs, hipStream_t s);
 hipError_t launch_sweep(int dtype, int order, int limiter, const SweepArgs& a,
                         const SweepPlan& p, const void* table, hipStream_t s);
 size_t pencil_table_bytes(int dtype, int64_t count);
@@ -136,6 +146,7 @@ struct LinePlan {
   int64_t blocks;      // number of blocks
   int64_t bstride;     // elements between blocks of row tiles
   int64_t tiles;
+  int32_t reps;        // block tiles: sweeps of the tile one after the other
   FastDiv32 dtpb, dvdiv, dnvl, dxdiv;
   size_t lds_bytes;    // 0: the sweep is not one this kernel takes
 };
@@ -211,6 +222,43 @@ constexpr int kBatchMaxSpace = 2048;  // spatial cells per run (one-workgroup Po
 // workgroups per CU) and hard limit
 constexpr size_t kBatchTileLds = 32 * 1024;
 constexpr size_t kBatchTileLdsMax = 96 * 1024;
+
+// ---- field solve (poisson.hip) ----
+// Sizes of the solve (D = 2 holds x_2 as the third axis): inputs n,
+// transform lengths m (2 n for isolated boundaries), outputs o (n + 2 halo),
+// twiddle offsets, columns and rows per workgroup or chunk, LDS bytes.
+struct FieldPlan {
+  int D, order, halo, ok;  // order: of the FDA; ok 0: not a size the kernels take
+  int n[3], m[3], o[3], tw[3];
+  int cols1, cols2, rows2, cols3;
+  size_t lds1, lds2, lds3;
+  double h[3];  // mesh spacing of component l
+};
+// Pencil tables of the velocity sweeps along v_l with the solved
+// acceleration (tab[l] null: none).
+struct FieldTables {
+  void* tab[3];
+  double h[3];
+  int32_t n[3];
+  int32_t bc, rk;
+  double dt;
+};
+FieldPlan plan_field(int D, const int64_t* nx, const double* h, int order, bool isolated);
+// Density (rho, or from row sums `part`: see field_forward_kernel) and its
+// transform along x_1 into bufA; then the rest, phi and accel.
+hipError_t launch_field_forward(const FieldPlan& p, const double* part, int nsub, double dvol,
+                                double* rho, double2* bufA, const double2* tw, hipStream_t s);
+hipError_t launch_field_rest(const FieldPlan& p, double* phi, double* accel, double2* bufA,
+                             double2* bufB, double* phi_ext, const double2* tw, const double* green,
+                             int dtype, int order, const FieldTables& tabs, hipStream_t s);
+// D = 1, up to kConvMax cells: the whole solve as a convolution of the
+// density with conv[0..n) (potential) and conv[n..2n) (acceleration).
+constexpr int kConvMax = 1024;
+hipError_t launch_conv_setup(int n, double h, int order, const double* green, const double2* tw,
+                             double* conv, hipStream_t s);
+hipError_t launch_field_conv(int n, const double* part, int nsub, double dvol, double* rho, double* phi,
+                             double* accel, const double* conv, int dtype, int order,
+                             const FieldTables& tabs, hipStream_t s);
 
 // ---- field kernels (field.hip) ----
 hipError_t launch_moment(int dtype, const void* f, int64_t nxs, int64_t nvs, double dvol,

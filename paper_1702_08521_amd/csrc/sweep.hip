@@ -211,10 +211,9 @@ SweepPlan plan_sweep(int dtype, int order, int limiter, int32_t n, int64_t npen,
   return p;
 }
 
-hipError_t launch_pencil_table(int dtype, int order, const SweepArgs& a, void* table,
-                               int64_t table_count, hipStream_t s) {
-  return dtype == SLMPP_F64 ? SweepLaunch<double>::table(order, a, table, (int)table_count, s)
-                            : SweepLaunch<float>::table(order, a, table, (int)table_count, s);
+hipError_t launch_tables(int dtype, int order, const TableJobs& jobs, hipStream_t s) {
+  return dtype == SLMPP_F64 ? SweepLaunch<double>::tables(order, jobs, s)
+                            : SweepLaunch<float>::tables(order, jobs, s);
 }
 
 hipError_t launch_sweep(int dtype, int order, int limiter, const SweepArgs& a, const SweepPlan& p,

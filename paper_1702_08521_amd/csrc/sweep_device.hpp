@@ -369,10 +369,9 @@ __device__ __forceinline__ void global_store_nt(V v, V* p) {
   __builtin_nontemporal_store(v, (GlobalPtr<V>)p);
 }
 
-// Pencil-table entry for speed index idx (see PencilEntry).
+// Pencil-table entry for speed c (see PencilEntry).
 template <typename T, int ORDER>
-__device__ __forceinline__ PencilEntry<T> pencil_entry(const SweepArgs& a, int idx) {
-  const double c = a.cmode == SPEED_FROM_VELOCITY ? cell_center(a.vlo, a.dv, idx) : a.accel[idx];
+__device__ __forceinline__ PencilEntry<T> pencil_entry_of(const SweepArgs& a, double c) {
   const double xi = departure(c, a.dt, a.h);
   const int n = a.n;
   double zeta;
@@ -425,6 +424,13 @@ __device__ __forceinline__ PencilEntry<T> pencil_entry(const SweepArgs& a, int i
     e.w[k] = (T)acc;
   }
   return e;
+}
+
+// Entry for speed index idx: a velocity cell centre or a spatial cell.
+template <typename T, int ORDER>
+__device__ __forceinline__ PencilEntry<T> pencil_entry(const SweepArgs& a, int idx) {
+  return pencil_entry_of<T, ORDER>(
+      a, a.cmode == SPEED_FROM_VELOCITY ? cell_center(a.vlo, a.dv, idx) : a.accel[idx]);
 }
 
 }  // namespace

@@ -877,10 +877,13 @@ __global__ void __launch_bounds__((PlaneShape<T, ORDER, N>::threads))
   }
 }
 
+// The tables of several sweeps in one launch (grid.y = table).
 template <typename T, int ORDER>
-__global__ void pencil_table_kernel(SweepArgs a, PencilEntry<T>* __restrict__ tab, int count) {
+__global__ void __launch_bounds__(128) pencil_table_kernel(TableJobs jobs) {
+  const int y = blockIdx.y;
   const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx < count) tab[idx] = pencil_entry<T, ORDER>(a, idx);
+  if (idx < jobs.count[y])
+    reinterpret_cast<PencilEntry<T>*>(jobs.tab[y])[idx] = pencil_entry<T, ORDER>(jobs.a[y], idx);
 }
 
 template <typename T, int ORDER, int LIM>
@@ -981,13 +984,6 @@ hipError_t launch_o(int limiter, const SweepArgs& a, const SweepPlan& p, const v
   }
 }
 
-template <typename T, int ORDER>
-hipError_t launch_table_t(const SweepArgs& a, void* table, int count, hipStream_t s) {
-  hipLaunchKernelGGL((pencil_table_kernel<T, ORDER>), dim3((count + 127) / 128), dim3(128), 0, s,
-                     a, reinterpret_cast<PencilEntry<T>*>(table), count);
-  return hipGetLastError();
-}
-
 // ---- grouped launches over many independent runs ----------------------
 template <typename T>
 __global__ void batch_table_kernel(const BatchSweep* __restrict__ sweeps) {
@@ -1084,8 +1080,16 @@ hipError_t launch_plane_o(const SweepArgs& a, const PlanePlan& p, const void* ta
 }  // namespace
 
 template <typename T>
-hipError_t SweepLaunch<T>::table(int order, const SweepArgs& a, void* tab, int count, hipStream_t s) {
-  return order == 7 ? launch_table_t<T, 7>(a, tab, count, s) : launch_table_t<T, 5>(a, tab, count, s);
+hipError_t SweepLaunch<T>::tables(int order, const TableJobs& jobs, hipStream_t s) {
+  int most = 0;
+  for (int k = 0; k < jobs.n; ++k) most = std::max(most, jobs.count[k]);
+  if (most <= 0) return hipSuccess;
+  const dim3 grid((most + 127) / 128, jobs.n);
+  if (order == 7)
+    hipLaunchKernelGGL((pencil_table_kernel<T, 7>), grid, dim3(128), 0, s, jobs);
+  else
+    hipLaunchKernelGGL((pencil_table_kernel<T, 5>), grid, dim3(128), 0, s, jobs);
+  return hipGetLastError();
 }
 
 template <typename T>

@@ -11,7 +11,7 @@ namespace slmpp {
 
 template <typename T>
 struct SweepLaunch {
-  static hipError_t table(int order, const SweepArgs& a, void* tab, int count, hipStream_t s);
+  static hipError_t tables(int order, const TableJobs& jobs, hipStream_t s);
   static hipError_t sweep(int order, int limiter, const SweepArgs& a, const SweepPlan& p,
                           const void* tab, hipStream_t s);
   static hipError_t kick_plane(int order, const SweepArgs& a, const PlanePlan& p, const void* tabA,

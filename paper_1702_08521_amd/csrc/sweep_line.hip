@@ -82,6 +82,13 @@ __device__ __forceinline__ void advance_line(const T* __restrict__ col, int rs, 
   }
 }
 
+// MODE of line_sweep_kernel: one sweep; all three TVD-RK stages; pl.reps
+// sweeps of block tiles one after the other (the same kick twice, with one
+// read and one write of f).  (Entries computed in the kernel instead of read
+// from a table cost small grids more in registers than the launch for the
+// table: 64 x 128 FP64, x sweep 9.0 -> 11.5 us.)
+enum : int { LINE_ONE = 0, LINE_RK = 1, LINE_REPEAT = 2 };
+
 // Persistent workgroups over tiles of whole pencils, the next tile's data
 // loaded into registers before the current one is computed, as in
 // sweep_fast_kernel, with every size a run-time value:
@@ -93,7 +100,7 @@ __device__ __forceinline__ void advance_line(const T* __restrict__ col, int rs, 
 // of R cells, the last one moved back to end at the pencil's end (the cells
 // it shares with the one before are computed twice, to the same bits).  For
 // the data movement it holds up to kLineMaxR elements in 16-byte vectors.
-// RK: all three TVD-RK stages on the tile in LDS, one read and one write of
+// LINE_RK: all three TVD-RK stages on the tile in LDS, one read and one write of
 // f instead of eight passes.
 //
 // Bound by HBM on large grids (18 x 20 x 24 x 30 x 36 x 42 FP32 SL-MPP7, 3.1 GB
@@ -107,9 +114,9 @@ __device__ __forceinline__ void advance_line(const T* __restrict__ col, int rs, 
 // 11.9 ms for that step), steps between a thread's vectors kept in scalar
 // registers, and loads without a second path for partial vectors (whose
 // merge made every load wait for the one before: 7.34 ms).
-template <typename T, int ORDER, int LIM, bool BLK, bool RK>
-__global__ void __attribute__((amdgpu_flat_work_group_size(1, RK ? kLineThreadsSmall : kLineThreads),
-                               amdgpu_waves_per_eu(RK ? 3 : 4)))
+template <typename T, int ORDER, int LIM, bool BLK, int MODE>
+__global__ void __attribute__((amdgpu_flat_work_group_size(1, MODE == LINE_RK ? kLineThreadsSmall : kLineThreads),
+                               amdgpu_waves_per_eu(MODE == LINE_RK ? 3 : (MODE == LINE_REPEAT ? 2 : 4))))
 line_sweep_kernel(SweepArgs a, LinePlan pl, const PencilEntry<T>* __restrict__ table) {
   extern __shared__ __align__(16) unsigned char smem[];
   using V = typename Vec<T>::type;
@@ -340,10 +347,24 @@ line_sweep_kernel(SweepArgs a, LinePlan pl, const PencilEntry<T>* __restrict__ t
           }
       }
     };
-    if constexpr (!RK) {
+    if constexpr (MODE != LINE_RK) {
       sweep_once();
       __syncthreads();
       keep();
+      if constexpr (MODE == LINE_REPEAT) {
+        // the closing half-kick of a step and the opening one of the next
+#pragma unroll 1
+        for (int rep = 1; rep < pl.reps; ++rep) {
+          __syncthreads();
+          if (periodic) {
+            fill_ghosts();
+            __syncthreads();
+          }
+          sweep_once();
+          __syncthreads();
+          keep();
+        }
+      }
     } else {
       // f1 = S(f), f2 = 3/4 f + 1/4 S(f1), 1/3 f + 2/3 S(f2)  (Eq. (RK))
       T fn[kLineMaxR<T>];
@@ -409,7 +430,7 @@ line_sweep_kernel(SweepArgs a, LinePlan pl, const PencilEntry<T>* __restrict__ t
         }
       }
     }
-    if constexpr (!BLK && !RK) {
+    if constexpr (!BLK && MODE != LINE_RK) {
       if (a.mom != nullptr) {
         // row sums for the velocity moment: 16 lanes per tile row, each its
         // vectors of the row in double, combined in a fixed order
@@ -439,9 +460,9 @@ line_sweep_kernel(SweepArgs a, LinePlan pl, const PencilEntry<T>* __restrict__ t
   }
 }
 
-template <typename T, int ORDER, int LIM, bool BLK, bool RK>
+template <typename T, int ORDER, int LIM, bool BLK, int MODE>
 hipError_t launch_t(const SweepArgs& a, const LinePlan& p, const void* table, hipStream_t s) {
-  auto kern = line_sweep_kernel<T, ORDER, LIM, BLK, RK>;
+  auto kern = line_sweep_kernel<T, ORDER, LIM, BLK, MODE>;
   const void* fn = reinterpret_cast<const void*>(kern);
   hipError_t e = hipSuccess;
   if (p.lds_bytes > 64 * 1024)
@@ -460,10 +481,11 @@ hipError_t launch_t(const SweepArgs& a, const LinePlan& p, const void* table, hi
 template <typename T, int ORDER, int LIM>
 hipError_t launch_l(const SweepArgs& a, const LinePlan& p, const void* table, hipStream_t s) {
   if (a.rk)
-    return p.K ? launch_t<T, ORDER, LIM, true, true>(a, p, table, s)
-               : launch_t<T, ORDER, LIM, false, true>(a, p, table, s);
-  return p.K ? launch_t<T, ORDER, LIM, true, false>(a, p, table, s)
-             : launch_t<T, ORDER, LIM, false, false>(a, p, table, s);
+    return p.K ? launch_t<T, ORDER, LIM, true, LINE_RK>(a, p, table, s)
+               : launch_t<T, ORDER, LIM, false, LINE_RK>(a, p, table, s);
+  if (p.K && p.reps > 1) return launch_t<T, ORDER, LIM, true, LINE_REPEAT>(a, p, table, s);
+  return p.K ? launch_t<T, ORDER, LIM, true, LINE_ONE>(a, p, table, s)
+             : launch_t<T, ORDER, LIM, false, LINE_ONE>(a, p, table, s);
 }
 
 template <typename T, int ORDER>
@@ -491,7 +513,8 @@ LinePlan plan_line(int dtype, int order, const SweepArgs& a, int64_t moment_bloc
   // enough, fewer on small grids, whose time is the latency of one thread's
   // segment
   const int64_t cells = a.npen * n;
-  const int Rt = cells >= ((int64_t)1 << 22) ? maxr : (cells >= ((int64_t)1 << 19) ? 8 : 4);
+  const int Rt = cells >= ((int64_t)1 << 22) ? maxr
+                 : (cells >= ((int64_t)1 << 19) || moment_block > 0 ? 8 : 4);
   const int64_t percell = (n + 2 * p.G) * es;  // LDS bytes per pencil
   int S = 0, pwmax = 0;
   auto tile_of = [&](int threads) {
@@ -545,7 +568,9 @@ LinePlan plan_line(int dtype, int order, const SweepArgs& a, int64_t moment_bloc
     int w = std::max(vn, pwmax / vn * vn);
     int64_t tpb = (p.blen + w - 1) / w;
     auto width = [&](int64_t tb) { return (int)(((p.blen + tb - 1) / tb + vn - 1) / vn * vn); };
-    while (tpb * p.blocks < kWant && width(2 * tpb) >= 8 && width(2 * tpb) * S >= 64) tpb *= 2;
+    // (row sums: fewer, wider tiles, whose sums the field solve adds up)
+    const int least = moment_block > 0 ? 64 : 8;
+    while (tpb * p.blocks < kWant && width(2 * tpb) >= least && width(2 * tpb) * S >= 64) tpb *= 2;
     p.W = width(tpb);
     p.tpb = (int)((p.blen + p.W - 1) / p.W);
     p.pw = p.W;
@@ -561,6 +586,7 @@ LinePlan plan_line(int dtype, int order, const SweepArgs& a, int64_t moment_bloc
   p.dvdiv = FastDiv32::of((uint32_t)std::max<int64_t>(1, std::min<int64_t>(a.vdiv, 0x7fffffff)));
   p.dnvl = FastDiv32::of((uint32_t)std::max(1, a.nvl));
   p.dxdiv = FastDiv32::of((uint32_t)std::max<int64_t>(1, std::min<int64_t>(a.xdiv, 0x7fffffff)));
+  p.reps = 1;
   p.lds_bytes = lds;
   return p;
 }
