@@ -118,10 +118,12 @@ typedef struct {
 
 /* flags: slmpp_step sweeps every velocity axis of a kick separately.
  * Without it, when D >= 2, the velocity boundaries are outflow, the limiter
- * is SLMPP_LIM_MPP, the time integration semi-Lagrangian and the last two
- * velocity axes have N x N cells with N in {24, 32, 48, 64}, the sweeps
- * along v_{D-1} and v_D of a kick are done in one pass over f (timing class
- * 7), with results equal to the separate sweeps bit for bit. */
+ * is SLMPP_LIM_MPP, the time integration semi-Lagrangian and the planes of
+ * the last two velocity axes have N x N cells with N in {24, 32, 48, 64}, or
+ * at least 8 cells along each axis, fit on the chip and have at least 1024
+ * cells or belong to a grid of at most 2^21, the sweeps along v_{D-1} and v_D
+ * of a kick are done in one pass over f (timing class 7), with results equal
+ * to the separate sweeps bit for bit. */
 #define SLMPP_FLAG_SEPARATE_KICKS 8
 
 typedef struct slmpp_ctx slmpp_ctx;
@@ -369,7 +371,7 @@ slmpp_status slmpp_batch_autotune(slmpp_batch* b, const char* cache_path);
  * alpha and largest fast shift) that the persistent single-run kernel
  * takes are advanced by one launch of it per phase when their cells add up
  * to at least min_cells (default 4194304); so are the v_{D-1} and v_D
- * sweeps of the kicks of runs with one velocity-plane geometry that the
+ * sweeps of the kicks of runs with one N x N velocity-plane geometry that the
  * two-axis pass of slmpp_step takes (see SLMPP_FLAG_SEPARATE_KICKS), as
  * one pass in the v_D phase.  A grouped x_1 phase whose tiles lie within
  * velocity blocks also leaves the tile row sums of the velocity moment

@@ -471,24 +471,31 @@ struct slmpp_ctx {
     return SLMPP_OK;
   }
 
-  // The two-axis pass of a kick (v_{D-1}, v_D), when its kernel takes this
-  // grid; else lds_bytes == 0.
-  PlanePlan kick_plane_plan() const {
+  // The two-axis pass of a kick (v_{D-1}, v_D), when one of its kernels takes
+  // this grid: compile-time square planes, else any; lds_bytes == 0 in both:
+  // neither.
+  void kick_pass_plans(PlanePlan& square, RectPlan& rect) const {
+    square = PlanePlan{};
+    rect = RectPlan{};
     if (D < 2 || rk || d.limiter != SLMPP_LIM_MPP || d.v_bc != SLMPP_BC_OUTFLOW ||
         (d.flags & SLMPP_FLAG_SEPARATE_KICKS))
-      return PlanePlan{};
+      return;
     int64_t vouter = 1;
     for (int l = 0; l < D - 2; ++l) vouter *= d.nv[l];
-    return plan_kick_plane(d.storage, d.order, (int32_t)d.nv[D - 2], (int32_t)d.nv[D - 1],
-                           nxs * vouter, vouter);
+    square = plan_kick_plane(d.storage, d.order, (int32_t)d.nv[D - 2], (int32_t)d.nv[D - 1],
+                             nxs * vouter, vouter);
+    if (!square.lds_bytes)
+      rect = plan_kick_rect(d.storage, d.order, d.nv[D - 2], d.nv[D - 1], nxs * vouter, vouter);
   }
 
   // The velocity sweeps of one kick, v_1 .. v_D in that order with the
   // current acceleration, whose tables for dt have been made; v_{D-1} and v_D
   // in one pass when possible.  kicks: that many kicks one after the other.
   slmpp_status kick(double dt, int kicks = 1) {
-    const PlanePlan pp = kick_plane_plan();
-    const int nsep = pp.lds_bytes ? D - 2 : D;
+    PlanePlan pp;
+    RectPlan rp;
+    kick_pass_plans(pp, rp);
+    const int nsep = pp.lds_bytes || rp.lds_bytes ? D - 2 : D;
     slmpp_status st = SLMPP_OK;
     for (int left = kicks; left > 0 && st == SLMPP_OK;) {
       int done = 1;
@@ -503,7 +510,9 @@ struct slmpp_ctx {
         const double cells = (double)ncell;
         hipError_t e = tic(7, 2.0 * cells * esize(), 2.0 * cells);
         if (e == hipSuccess)
-          e = launch_kick_plane(d.storage, d.order, s, pp, table(2 * D - 2), table(2 * D - 1), stream);
+          e = pp.lds_bytes
+                  ? launch_kick_plane(d.storage, d.order, s, pp, table(2 * D - 2), table(2 * D - 1), stream)
+                  : launch_kick_rect(d.storage, d.order, s, rp, table(2 * D - 2), table(2 * D - 1), stream);
         if (e == hipSuccess) e = toc();
         if (e != hipSuccess) st = hip_fail(e, "kick launch");
       }

@@ -160,6 +160,21 @@ PlanePlan plan_kick_plane(int dtype, int order, int32_t na, int32_t nb, int64_t 
 hipError_t launch_kick_plane(int dtype, int order, const SweepArgs& a, const PlanePlan& p,
                              const void* tabA, const void* tabB, hipStream_t s);
 
+// The same pass for planes of any na x nb cells (kick_rect_kernel): one plane
+// per tile, f[p na nb ..), tables as above.
+struct RectPlan {
+  int32_t na, nb;      // cells along v_{D-1}, v_D
+  int32_t sa, ra, sb, rb;  // segments and cells per segment of the two sweeps
+  int32_t G, pitch;    // ring of zero cells in LDS, LDS row pitch
+  int32_t threads;
+  int64_t planes;
+  FastDiv32 vdiv;      // plane -> spatial cell
+  size_t lds_bytes;    // 0: not a size the kernel takes
+};
+RectPlan plan_kick_rect(int dtype, int order, int64_t na, int64_t nb, int64_t planes, int64_t vouter);
+hipError_t launch_kick_rect(int dtype, int order, const SweepArgs& a, const RectPlan& p,
+                            const void* tabA, const void* tabB, hipStream_t s);
+
 // Integer-shift bound of a sweep along x_l: max |N| over the velocity
 // centres of axis l, with the same split as the kernels.
 int32_t max_shift_velocity(double vlo, double dv, int32_t nvl, double dt, double h, int32_t n,

@@ -369,6 +369,86 @@ __device__ __forceinline__ void global_store_nt(V v, V* p) {
   __builtin_nontemporal_store(v, (GlobalPtr<V>)p);
 }
 
+// 16-byte vectors at element-aligned addresses (rows and blocks of odd
+// length start anywhere; the hardware takes any 4-byte address)
+template <typename T>
+struct UVec;
+template <>
+struct UVec<float> {
+  typedef float type __attribute__((ext_vector_type(4), aligned(4)));
+};
+template <>
+struct UVec<double> {
+  typedef double type __attribute__((ext_vector_type(2), aligned(8)));
+};
+
+// Advance cells m0 .. m0 + R - 1 (processing order) of the pencil whose
+// physical cell 0 is at col, cells rs elements apart; R <= MAXR, the
+// same for the whole launch (the loop is unrolled with a scalar exit).
+// SAFE: reads wrap (periodic) or stop at the zero ghost cells (outflow).
+template <typename T, int ORDER, int LIM, bool SAFE, int MAXR>
+__device__ __forceinline__ void advance_line(const T* __restrict__ col, int rs, int n, int G,
+                                             int periodic, const PencilEntry<T>& e, int m0, int R,
+                                             T alpha, T* out) {
+  constexpr int H = (ORDER == 7) ? 3 : 2;
+  constexpr int WIN = 2 * H + 1;
+  int r = e.base + e.dir * (m0 - 1 - H);
+  const T* ptr = col + r * rs;
+  const int step = e.dir * rs;
+  auto fetch = [&]() -> T {
+    if constexpr (!SAFE) {
+      const T v = *ptr;
+      ptr += step;
+      return v;
+    } else {
+      int rr = r;
+      if (periodic) {
+        rr %= n;
+        if (rr < 0) rr += n;
+      } else {
+        rr = min(max(rr, -G), n + G - 1);
+      }
+      r += e.dir;
+      return col[rr * rs];
+    }
+  };
+  T q[MAXR + WIN];
+#pragma unroll
+  for (int k = 0; k < WIN; ++k) q[k] = fetch();
+  T f_left = face_flux<T, ORDER, LIM>(q, e.w, e.tz, alpha);
+#pragma unroll
+  for (int k = 0; k < MAXR; ++k) {
+    if (k < R) {
+      q[k + WIN] = fetch();
+      const T f_right = face_flux<T, ORDER, LIM>(q + k + 1, e.w, e.tz, alpha);
+      out[k] = vfma(-e.z, f_right - f_left, q[k + 1 + H]);
+      f_left = f_right;
+    }
+  }
+}
+
+// A pencil entry read through the constant address space: the tables are
+// not written while a sweep runs, so where the address is uniform over the
+// wavefront the compiler loads the entry with scalar loads and keeps it in
+// scalar registers (its weights then enter the FMAs as scalar operands).
+template <typename T>
+__device__ __forceinline__ PencilEntry<T> load_entry_uniform(const PencilEntry<T>* p) {
+  constexpr int NW = sizeof(PencilEntry<T>) / 4;
+  using CW = const __attribute__((address_space(4))) uint32_t*;
+  const CW q = (CW)(p);
+  uint32_t w[NW];
+#pragma unroll
+  for (int i = 0; i < NW; ++i) w[i] = q[i];
+  PencilEntry<T> e;
+  __builtin_memcpy(&e, w, sizeof(e));
+  return e;
+}
+template <typename P>
+__device__ __forceinline__ P load_ptr_uniform(const P* p) {
+  using CU = const __attribute__((address_space(4))) uint64_t*;
+  return reinterpret_cast<P>(static_cast<uintptr_t>(*(CU)(p)));
+}
+
 // Pencil-table entry for speed c (see PencilEntry).
 template <typename T, int ORDER>
 __device__ __forceinline__ PencilEntry<T> pencil_entry_of(const SweepArgs& a, double c) {

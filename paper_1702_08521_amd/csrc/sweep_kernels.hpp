@@ -691,28 +691,6 @@ sweep_fast_kernel(SweepArgs a, SweepPlan pl,
 // workgroup with one segment per wavefront were measured slower than one
 // plane per workgroup: 33-38 ms against 25 ms per pass at 48^3 x 48^3, for
 // want of wavefronts per CU.)
-// A pencil entry read through the constant address space: the tables are
-// not written while a sweep runs, so where the address is uniform over the
-// wavefront the compiler loads the entry with scalar loads and keeps it in
-// scalar registers (its weights then enter the FMAs as scalar operands).
-template <typename T>
-__device__ __forceinline__ PencilEntry<T> load_entry_uniform(const PencilEntry<T>* p) {
-  constexpr int NW = sizeof(PencilEntry<T>) / 4;
-  using CW = const __attribute__((address_space(4))) uint32_t*;
-  const CW q = (CW)(p);
-  uint32_t w[NW];
-#pragma unroll
-  for (int i = 0; i < NW; ++i) w[i] = q[i];
-  PencilEntry<T> e;
-  __builtin_memcpy(&e, w, sizeof(e));
-  return e;
-}
-template <typename P>
-__device__ __forceinline__ P load_ptr_uniform(const P* p) {
-  using CU = const __attribute__((address_space(4))) uint64_t*;
-  return reinterpret_cast<P>(static_cast<uintptr_t>(*(CU)(p)));
-}
-
 template <typename T, int ORDER, int N, bool UNI>
 __global__ void __launch_bounds__((PlaneShape<T, ORDER, N>::threads))
     kick_plane_kernel(SweepArgs a, PlanePlan pl, const PencilEntry<T>* __restrict__ tabA,

@@ -23,65 +23,6 @@ constexpr int kLineThreads = 512, kLineThreadsSmall = 256;
 constexpr size_t kLineLds = 40 * 1024;     // preferred LDS of a tile: four workgroups per CU
 constexpr size_t kLineLdsMax = 80 * 1024;  // at most (long pencils)
 
-// 16-byte vectors at element-aligned addresses (rows and blocks of odd
-// length start anywhere; the hardware takes any 4-byte address)
-template <typename T>
-struct UVec;
-template <>
-struct UVec<float> {
-  typedef float type __attribute__((ext_vector_type(4), aligned(4)));
-};
-template <>
-struct UVec<double> {
-  typedef double type __attribute__((ext_vector_type(2), aligned(8)));
-};
-
-// Advance cells m0 .. m0 + R - 1 (processing order) of the pencil whose
-// physical cell 0 is at col, cells rs elements apart; R <= kLineMaxR, the
-// same for the whole launch (the loop is unrolled with a scalar exit).
-// SAFE: reads wrap (periodic) or stop at the zero ghost cells (outflow).
-// fn, where not null, receives the cells' own values (TVD-RK: no shift).
-template <typename T, int ORDER, int LIM, bool SAFE>
-__device__ __forceinline__ void advance_line(const T* __restrict__ col, int rs, int n, int G,
-                                             int periodic, const PencilEntry<T>& e, int m0, int R,
-                                             T alpha, T* out) {
-  constexpr int H = (ORDER == 7) ? 3 : 2;
-  constexpr int WIN = 2 * H + 1;
-  int r = e.base + e.dir * (m0 - 1 - H);
-  const T* ptr = col + r * rs;
-  const int step = e.dir * rs;
-  auto fetch = [&]() -> T {
-    if constexpr (!SAFE) {
-      const T v = *ptr;
-      ptr += step;
-      return v;
-    } else {
-      int rr = r;
-      if (periodic) {
-        rr %= n;
-        if (rr < 0) rr += n;
-      } else {
-        rr = min(max(rr, -G), n + G - 1);
-      }
-      r += e.dir;
-      return col[rr * rs];
-    }
-  };
-  T q[kLineMaxR<T> + WIN];
-#pragma unroll
-  for (int k = 0; k < WIN; ++k) q[k] = fetch();
-  T f_left = face_flux<T, ORDER, LIM>(q, e.w, e.tz, alpha);
-#pragma unroll
-  for (int k = 0; k < kLineMaxR<T>; ++k) {
-    if (k < R) {
-      q[k + WIN] = fetch();
-      const T f_right = face_flux<T, ORDER, LIM>(q + k + 1, e.w, e.tz, alpha);
-      out[k] = vfma(-e.z, f_right - f_left, q[k + 1 + H]);
-      f_left = f_right;
-    }
-  }
-}
-
 // MODE of line_sweep_kernel: one sweep; all three TVD-RK stages; pl.reps
 // sweeps of block tiles one after the other (the same kick twice, with one
 // read and one write of f).  (Entries computed in the kernel instead of read
@@ -330,9 +271,9 @@ line_sweep_kernel(SweepArgs a, LinePlan pl, const PencilEntry<T>* __restrict__ t
     auto sweep_once = [&]() __attribute__((always_inline)) {
       if (act) {
         if (!safe)
-          advance_line<T, ORDER, LIM, false>(col, rs, n, G, periodic, e, m0, R, alpha, out);
+          advance_line<T, ORDER, LIM, false, kLineMaxR<T>>(col, rs, n, G, periodic, e, m0, R, alpha, out);
         else
-          advance_line<T, ORDER, LIM, true>(col, rs, n, G, periodic, e, m0, R, alpha, out);
+          advance_line<T, ORDER, LIM, true, kLineMaxR<T>>(col, rs, n, G, periodic, e, m0, R, alpha, out);
       }
     };
     auto keep = [&]() __attribute__((always_inline)) {
