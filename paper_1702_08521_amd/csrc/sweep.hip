@@ -224,9 +224,9 @@ hipError_t launch_sweep(int dtype, int order, int limiter, const SweepArgs& a, c
 
 namespace {
 // the host's copy of PlaneShape
-template <typename T, int ORDER, int N>
+template <typename T, int ORDER, int N, int PB>
 void plane_shape(PlanePlan& p) {
-  using Sh = PlaneShape<T, ORDER, N>;
+  using Sh = PlaneShape<T, ORDER, N, PB>;
   p.N = N;
   p.PB = Sh::PB;
   p.G = Sh::G;
@@ -234,12 +234,15 @@ void plane_shape(PlanePlan& p) {
   p.plane_lds = Sh::PS;
 }
 template <typename T, int ORDER>
-bool plane_shape_n(int N, PlanePlan& p) {
-  switch (N) {
-    case 24: plane_shape<T, ORDER, 24>(p); return true;
-    case 32: plane_shape<T, ORDER, 32>(p); return true;
-    case 48: plane_shape<T, ORDER, 48>(p); return true;
-    case 64: plane_shape<T, ORDER, 64>(p); return true;
+bool plane_shape_n(int N, int64_t vouter, PlanePlan& p) {
+  const int pb = plane_count(sizeof(T) == 8, N, vouter);
+  switch (N * 10 + pb) {
+    case 244: plane_shape<T, ORDER, 24, 4>(p); return true;
+    case 242: plane_shape<T, ORDER, 24, 2>(p); return true;
+    case 322: plane_shape<T, ORDER, 32, 2>(p); return true;
+    case 321: plane_shape<T, ORDER, 32, 1>(p); return true;
+    case 481: plane_shape<T, ORDER, 48, 1>(p); return true;
+    case 641: plane_shape<T, ORDER, 64, 1>(p); return true;
     default: return false;
   }
 }
@@ -251,8 +254,8 @@ PlanePlan plan_kick_plane(int dtype, int order, int32_t na, int32_t nb, int64_t 
   if (na != nb || !(na == 24 || na == 32 || na == 48 || na == 64) || planes < 1 || vouter < 1)
     return p;
   const bool ok = dtype == SLMPP_F64
-                      ? (order == 7 ? plane_shape_n<double, 7>(na, p) : plane_shape_n<double, 5>(na, p))
-                      : (order == 7 ? plane_shape_n<float, 7>(na, p) : plane_shape_n<float, 5>(na, p));
+                      ? (order == 7 ? plane_shape_n<double, 7>(na, vouter, p) : plane_shape_n<double, 5>(na, vouter, p))
+                      : (order == 7 ? plane_shape_n<float, 7>(na, vouter, p) : plane_shape_n<float, 5>(na, vouter, p));
   if (!ok) return PlanePlan{};
   p.planes = planes;
   p.vouter = vouter;

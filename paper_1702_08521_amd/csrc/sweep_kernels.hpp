@@ -691,13 +691,13 @@ sweep_fast_kernel(SweepArgs a, SweepPlan pl,
 // workgroup with one segment per wavefront were measured slower than one
 // plane per workgroup: 33-38 ms against 25 ms per pass at 48^3 x 48^3, for
 // want of wavefronts per CU.)
-template <typename T, int ORDER, int N, bool UNI>
-__global__ void __launch_bounds__((PlaneShape<T, ORDER, N>::threads))
+template <typename T, int ORDER, int N, int PLANES, bool UNI>
+__global__ void __launch_bounds__((PlaneShape<T, ORDER, N, PLANES>::threads))
     kick_plane_kernel(SweepArgs a, PlanePlan pl, const PencilEntry<T>* __restrict__ tabA,
                       const PencilEntry<T>* __restrict__ tabB) {
   extern __shared__ __align__(16) unsigned char smem[];
   using V = typename Vec<T>::type;
-  using Sh = PlaneShape<T, ORDER, N>;
+  using Sh = PlaneShape<T, ORDER, N, PLANES>;
   constexpr int VN = Vec<T>::N;
   constexpr int R = Sh::R, S = Sh::S, PB = Sh::PB, NT = Sh::threads;
   constexpr int G = Sh::G, P = Sh::P, PS = Sh::PS;
@@ -1002,17 +1002,17 @@ __global__ void __launch_bounds__(256) batch_sweep_kernel(const BatchSweep* __re
   }
 }
 
-template <typename T, int ORDER, int N, bool UNI>
+template <typename T, int ORDER, int N, int PB, bool UNI>
 hipError_t launch_plane_u(const SweepArgs& a, const PlanePlan& p, const void* tabA,
                           const void* tabB, hipStream_t s) {
-  auto kern = kick_plane_kernel<T, ORDER, N, UNI>;
+  auto kern = kick_plane_kernel<T, ORDER, N, PB, UNI>;
   if (p.lds_bytes > 64 * 1024) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                        hipFuncAttributeMaxDynamicSharedMemorySize,
                                        (int)p.lds_bytes);
     if (e != hipSuccess) return e;
   }
-  constexpr int NT = PlaneShape<T, ORDER, N>::threads;
+  constexpr int NT = PlaneShape<T, ORDER, N, PB>::threads;
   int per_cu = 0;
   hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
       &per_cu, reinterpret_cast<const void*>(kern), NT, p.lds_bytes);
@@ -1025,8 +1025,9 @@ hipError_t launch_plane_u(const SweepArgs& a, const PlanePlan& p, const void* ta
     if (e != hipSuccess) return e;
   }
   // at most seven wavefronts per SIMD: with all eight slots taken the 24^2
-  // planes took 1085 against 973 us (32^3 x 24^3 FP32) and the 64^2 planes
-  // 207 against 180 us (15 runs of 32^2 x 64^2); 48^2 planes 20.8 ms either way
+  // planes in twos took 390 against 319 us (24^3 x 20x24^2 FP32) and the 64^2
+  // planes 207 against 180 us (15 runs of 32^2 x 64^2); 48^2 planes 20.8 ms
+  // either way
   constexpr int kWaves = (NT + 63) / 64;
   per_cu = std::min(per_cu, std::max(1, 28 / kWaves));
   const int64_t grid = std::min<int64_t>(p.tiles, (int64_t)std::max(per_cu, 1) * std::max(n_cu, 1));
@@ -1036,23 +1037,29 @@ hipError_t launch_plane_u(const SweepArgs& a, const PlanePlan& p, const void* ta
   return hipGetLastError();
 }
 
-template <typename T, int ORDER, int N>
-hipError_t launch_plane_t(const SweepArgs& a, const PlanePlan& p, const void* tabA,
-                          const void* tabB, hipStream_t s) {
-  return p.uni ? launch_plane_u<T, ORDER, N, true>(a, p, tabA, tabB, s)
-               : launch_plane_u<T, ORDER, N, false>(a, p, tabA, tabB, s);
-}
-
 template <typename T, int ORDER>
 hipError_t launch_plane_o(const SweepArgs& a, const PlanePlan& p, const void* tabA,
                           const void* tabB, hipStream_t s) {
-  switch (p.N) {
-    case 24: return launch_plane_t<T, ORDER, 24>(a, p, tabA, tabB, s);
-    case 32: return launch_plane_t<T, ORDER, 32>(a, p, tabA, tabB, s);
-    case 48: return launch_plane_t<T, ORDER, 48>(a, p, tabA, tabB, s);
-    case 64: return launch_plane_t<T, ORDER, 64>(a, p, tabA, tabB, s);
-    default: return hipErrorInvalidValue;
+  constexpr bool f32 = sizeof(T) == 4;
+  switch (p.N * 10 + p.PB) {
+    case 244:
+      if constexpr (f32) return launch_plane_u<T, ORDER, 24, 4, true>(a, p, tabA, tabB, s);
+      break;
+    case 242:
+      return p.uni ? launch_plane_u<T, ORDER, 24, 2, true>(a, p, tabA, tabB, s)
+                   : launch_plane_u<T, ORDER, 24, 2, false>(a, p, tabA, tabB, s);
+    case 322:
+      if (p.uni) return launch_plane_u<T, ORDER, 32, 2, true>(a, p, tabA, tabB, s);
+      if constexpr (f32) return launch_plane_u<T, ORDER, 32, 2, false>(a, p, tabA, tabB, s);
+      break;
+    case 321:
+      if constexpr (!f32) return launch_plane_u<T, ORDER, 32, 1, true>(a, p, tabA, tabB, s);
+      break;
+    case 481: return launch_plane_u<T, ORDER, 48, 1, true>(a, p, tabA, tabB, s);
+    case 641: return launch_plane_u<T, ORDER, 64, 1, true>(a, p, tabA, tabB, s);
+    default: break;
   }
+  return hipErrorInvalidValue;
 }
 
 }  // namespace

@@ -27,13 +27,26 @@ extern template struct SweepLaunch<double>;
 
 constexpr int kPlaneFast = 4;  // integer shifts read directly in the plane kernel
 
-template <typename T, int ORDER, int N>
+// Planes per tile, for planes of which vouter in a row share their two pencil
+// entries.  A tile within one such row reads the entries with scalar loads,
+// and 24^2 planes in twos (fours) of four 6-cell segments fill whole
+// wavefronts: at 24^3 x 20x24^2 the pass takes 307 us in FP32 with four planes
+// (319 with two, 357 with three of 8-cell segments, whose last wavefront is
+// 3/8 full) and 876 in FP64 with two (1062 with 8-cell segments).  FP64 32^2
+// planes in twos keep one segment per wavefront: 595 against 608 us at 20^3 x
+// 20x32^2, but 80 against 71 us at 132^2 x 32^2, where the planes of a tile
+// would not share their entries.
+constexpr int plane_count(bool f64, int N, int64_t vouter) {
+  return N == 24 ? (!f64 && vouter % 4 == 0 ? 4 : 2) : N == 32 ? (!f64 || vouter % 2 == 0 ? 2 : 1) : 1;
+}
+
+template <typename T, int ORDER, int N, int PLANES>
 struct PlaneShape {
   // cells per thread (FP32 64^2 planes: 512 threads of 8 cells, whose extra
   // waves outweigh the segment-boundary faces they add)
-  static constexpr int R = N == 64 ? (sizeof(T) == 4 ? 8 : 16) : (N == 48 ? 12 : 8);
+  static constexpr int R = N == 64 ? (sizeof(T) == 4 ? 8 : 16) : N == 48 ? 12 : N == 32 ? 8 : 6;
   static constexpr int S = N / R;                               // segments per pencil
-  static constexpr int PB = sizeof(T) == 4 ? (N == 24 ? 3 : N == 32 ? 2 : 1) : (N == 24 ? 2 : 1);
+  static constexpr int PB = PLANES;
   static constexpr int threads = PB * N * S;
   // ring width (shifts up to kPlaneFast cells read the ring directly)
   static constexpr int G = (ORDER == 7 ? 4 : 3) + kPlaneFast;
