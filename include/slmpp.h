@@ -139,7 +139,9 @@ typedef struct {
 
 /* Per-kernel-class timing gathered with HIP events on the context stream. */
 #define SLMPP_TIMING_CLASSES 8 /* 0: sweeps along a strided axis, tiles of
-                                     128 or 256 pencils,
+                                     128 or 256 pencils, and the x_3 and x_2
+                                     sweeps of a step in one pass (two cell
+                                     updates per cell),
                                   1: sweeps along the contiguous axis,
                                   2: velocity moment, 3: Poisson + force,
                                   4: sweeps along a strided axis, other tiles,

@@ -471,6 +471,27 @@ struct slmpp_ctx {
     return SLMPP_OK;
   }
 
+  // The x sweeps of a step, x_D .. x_1, whose tables have been made; x_3 and
+  // x_2 in one pass where its kernel takes the grid.  *fused as for sweep().
+  slmpp_status x_block(double dt, bool* fused) {
+    int l = D - 1;
+    if (D == 3 && !rk && d.limiter == SLMPP_LIM_MPP) {
+      const SweepArgs sa = sweep_args(1, dt, nullptr), sb = sweep_args(2, dt, nullptr);
+      const PairPlan pp = plan_pair(d.storage, sa, sb, d.nx[0]);
+      if (pp.lds_bytes) {
+        const double cells = (double)ncell;
+        hipError_t e = tic(0, 2.0 * cells * esize(), 2.0 * cells);
+        if (e == hipSuccess) e = launch_pair(d.storage, d.order, sa, pp, table(1), table(2), stream);
+        if (e == hipSuccess) e = toc();
+        if (e != hipSuccess) return hip_fail(e, "x sweep launch");
+        l = 0;
+      }
+    }
+    slmpp_status st = SLMPP_OK;
+    for (; l >= 0 && st == SLMPP_OK; --l) st = sweep(l, sweep_args(l, dt, nullptr), l == 0, fused);
+    return st;
+  }
+
   // The two-axis pass of a kick (v_{D-1}, v_D), when one of its kernels takes
   // this grid: compile-time square planes, else any; lds_bytes == 0 in both:
   // neither.
@@ -1096,8 +1117,7 @@ slmpp_status slmpp_step(slmpp_ctx* c, double dt, int32_t nsteps) {
   for (int32_t it = 0; it < nsteps && st == SLMPP_OK; ++it) {
     bool fused = false;
     const bool last = it + 1 == nsteps;
-    for (int l = D - 1; l >= 0 && st == SLMPP_OK; --l)
-      st = c->sweep(l, c->sweep_args(l, dt, nullptr), l == 0, &fused);
+    st = c->x_block(dt, &fused);
     const double next = merged && !last ? dt : half;
     if (st == SLMPP_OK) st = c->field(next, fused);
     if (st == SLMPP_OK) st = c->kick(next, merged || last ? 1 : 2);

@@ -175,6 +175,23 @@ RectPlan plan_kick_rect(int dtype, int order, int64_t na, int64_t nb, int64_t pl
 hipError_t launch_kick_rect(int dtype, int order, const SweepArgs& a, const RectPlan& p,
                             const void* tabA, const void* tabB, hipStream_t s);
 
+// The sweeps along x_3 and x_2 in one pass (pair_sweep_kernel): tiles of all
+// nA x nB (x_2, x_3) of one x_1 and 128 bytes of consecutive velocities.
+struct PairPlan {
+  int32_t nA, nB;          // cells along x_2, x_3
+  int32_t sA, rA, kA;      // x_2 sweep: segments, cells per segment, x_3 per round
+  int32_t sB, rB, kB;      // x_3 sweep: segments, cells per segment, x_2 per round
+  int32_t nvA, nvB;        // table entries of the two sweeps
+  int32_t threads, tiles, nch;  // nch: tiles of one x_1
+  int32_t inner32;
+  int64_t inner;           // elements between rows: velocities of a spatial cell
+  FastDiv32 dch, dvA, dvB, dnA, dnB;
+  size_t lds_bytes;        // 0: not a grid the kernel takes
+};
+PairPlan plan_pair(int dtype, const SweepArgs& sA, const SweepArgs& sB, int64_t outer);
+hipError_t launch_pair(int dtype, int order, const SweepArgs& a, const PairPlan& p, const void* tabA,
+                       const void* tabB, hipStream_t s);
+
 // Integer-shift bound of a sweep along x_l: max |N| over the velocity
 // centres of axis l, with the same split as the kernels.
 int32_t max_shift_velocity(double vlo, double dv, int32_t nvl, double dt, double h, int32_t n,
