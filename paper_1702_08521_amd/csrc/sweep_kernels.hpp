@@ -691,8 +691,14 @@ sweep_fast_kernel(SweepArgs a, SweepPlan pl,
 // workgroup with one segment per wavefront were measured slower than one
 // plane per workgroup: 33-38 ms against 25 ms per pass at 48^3 x 48^3, for
 // want of wavefronts per CU.)
+// FP64 48^2 planes are held to 128 VGPRs (132 without): LDS fits four
+// workgroups of three wavefronts per CU, and with only three wavefronts per
+// SIMD their twelve fill the CU exactly, where some launches placed but three
+// workgroups and ran the fourth after them (48^3 x 48^3: 78 ms in such
+// launches, 51 in others; held to 128: 49 in all).
 template <typename T, int ORDER, int N, int PLANES, bool UNI>
-__global__ void __launch_bounds__((PlaneShape<T, ORDER, N, PLANES>::threads))
+__global__ void __attribute__((amdgpu_flat_work_group_size(1, PlaneShape<T, ORDER, N, PLANES>::threads),
+                               amdgpu_waves_per_eu(N == 48 && sizeof(T) == 8 ? 4 : 1)))
     kick_plane_kernel(SweepArgs a, PlanePlan pl, const PencilEntry<T>* __restrict__ tabA,
                       const PencilEntry<T>* __restrict__ tabB) {
   extern __shared__ __align__(16) unsigned char smem[];
@@ -714,11 +720,18 @@ __global__ void __launch_bounds__((PlaneShape<T, ORDER, N, PLANES>::threads))
   // rings); the barrier orders these stores before the first tile's data
   for (int e = tid; e < PB * PS; e += NT) lds[e] = T(0);
   __syncthreads();
-  // data movement map: vector k of this thread is tile vector tid + NT k,
-  // in plane vq[k] (PB: none) at LDS offset loff[k]
-  int loff[NV], vq[NV];
+  // data movement map: vector k of this thread is tile vector tid + NT k, in
+  // plane plane_of(k) (PB: none) at LDS offset off_of(k).  Where NT vectors
+  // are whole rows and planes whole multiples of them, both follow from k at
+  // compile time and one register holds the map: FP64 48^2 planes 53.2 -> 49.3
+  // ms at 48^3 x 48^3 (no values spilled under their bound of 128 VGPRs,
+  // instead of 8), 64^2 562 -> 455 us at 12^3 x 20x64^2 and FP32 230 -> 212,
+  // FP64 32^2 605 -> 530 at 20^3 x 20x32^2.  FP32 32^2 and 48^2 planes, whose
+  // registers do not bound them, are 3-8% slower so (262 against 243 us).
+  constexpr bool STEP = (sizeof(T) == 8 || N == 64) && NN % (VN * NT) == 0 && (VN * NT) % N == 0;
+  int loff[STEP ? 1 : NV], vq[STEP ? 1 : NV];
 #pragma unroll
-  for (int k = 0; k < NV; ++k) {
+  for (int k = 0; k < (STEP ? 1 : NV); ++k) {
     const int v = tid + NT * k;
     if (v < NVEC) {
       const int e = v * VN;
@@ -731,6 +744,12 @@ __global__ void __launch_bounds__((PlaneShape<T, ORDER, N, PLANES>::threads))
       vq[k] = PB;
     }
   }
+  auto plane_of = [&](int k) __attribute__((always_inline)) -> int {
+    return STEP ? k * VN * NT / NN : vq[STEP ? 0 : k];
+  };
+  auto off_of = [&](int k) __attribute__((always_inline)) -> int {
+    return STEP ? loff[0] + k * VN * NT / NN * PS + k * VN * NT % NN / N * P : loff[STEP ? 0 : k];
+  };
   // compute map (segment-major): plane cq, pencil cj, cells m0 .. m0 + R - 1
   // of segment s.  With four segments and a wavefront holding parts of two,
   // the segments are laid out in the order 2, 0, 3, 1 (wavefronts hold
@@ -776,7 +795,7 @@ __global__ void __launch_bounds__((PlaneShape<T, ORDER, N, PLANES>::threads))
     const V* src = reinterpret_cast<const V*>(f_next + p0_next * NN);
 #pragma unroll
     for (int k = 0; k < NV; ++k)
-      if (vq[k] < np_next) pf[k] = __builtin_nontemporal_load(src + tid + NT * k);
+      if (plane_of(k) < np_next) pf[k] = __builtin_nontemporal_load(src + tid + NT * k);
   };
   int64_t t = blockIdx.x;
   if (t < pl.tiles) issue(t);
@@ -797,7 +816,7 @@ __global__ void __launch_bounds__((PlaneShape<T, ORDER, N, PLANES>::threads))
     }
 #pragma unroll
     for (int k = 0; k < NV; ++k)
-      if (vq[k] < np) put(lds + loff[k], pf[k]);
+      if (plane_of(k) < np) put(lds + off_of(k), pf[k]);
     __syncthreads();
     if (t + gridDim.x < pl.tiles) issue(t + gridDim.x);
     T out[R];
@@ -844,9 +863,9 @@ __global__ void __launch_bounds__((PlaneShape<T, ORDER, N, PLANES>::threads))
     V* dst = reinterpret_cast<V*>(fc + p0 * NN);
 #pragma unroll
     for (int k = 0; k < NV; ++k) {
-      if (vq[k] < np) {
+      if (plane_of(k) < np) {
         V v;
-        get(lds + loff[k], v);
+        get(lds + off_of(k), v);
         __builtin_nontemporal_store(v, dst + tid + NT * k);
       }
     }
