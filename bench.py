@@ -64,9 +64,11 @@ def read_traffic(kernel_key):
         return None
     import hashlib
 
-    src = os.path.join(ROOT, "paper_1702_08521_amd", "csrc", "sweep.hip")
-    h = hashlib.sha256(open(src, "rb").read()).hexdigest()[:16]
-    if ent.get("sweep_src_sha") != h:
+    h = hashlib.sha256()
+    for name in ("sweep_device.hpp", "sweep_kernels.hpp"):
+        with open(os.path.join(ROOT, "paper_1702_08521_amd", "csrc", name), "rb") as src:
+            h.update(src.read())
+    if ent.get("sweep_src_sha") != h.hexdigest()[:16]:
         return None
     return ent.get("bytes_per_launch")
 
