@@ -608,16 +608,16 @@ struct slmpp_ctx {
   }
 
   // The context's field (from the row sums of the x_1 sweep just done, or
-  // from f) and the tables of a kick by kick_dt with it (0: none).
-  slmpp_status field(double kick_dt = 0.0, bool rowsums = false) {
+  // from f) and, with a kick to follow, its tables for *kick_dt (null: none).
+  slmpp_status field(const double* kick_dt = nullptr, bool rowsums = false) {
     slmpp_status st = rowsums ? SLMPP_OK : moment(rho());
     bool with_tables = false;
-    const FieldTables tabs = kick_dt != 0.0 ? v_tables(kick_dt) : FieldTables{};
+    const FieldTables tabs = kick_dt ? v_tables(*kick_dt) : FieldTables{};
     if (st == SLMPP_OK)
       st = poisson(rho(), phi(), accel(), rowsums ? mom() : nullptr, tabs, &with_tables);
-    if (st == SLMPP_OK && kick_dt != 0.0 && !with_tables) {
+    if (st == SLMPP_OK && kick_dt && !with_tables) {
       TableJobs jobs{};
-      add_v_tables(jobs, kick_dt);
+      add_v_tables(jobs, *kick_dt);
       st = make_tables(jobs);
     }
     if (st == SLMPP_OK) field_valid = true;
@@ -625,18 +625,16 @@ struct slmpp_ctx {
   }
 
   // field, if f changed since the last one, and the tables of a kick by
-  // kick_dt; with x_dt != 0 those of the x sweeps too
-  slmpp_status prepare(double kick_dt, double x_dt) {
+  // kick_dt; with x_dt those of the x sweeps by *x_dt too
+  slmpp_status prepare(double kick_dt, const double* x_dt) {
     TableJobs jobs{};
-    if (x_dt != 0.0)
-      for (int l = 0; l < D; ++l) jobs.add(sweep_args(l, x_dt, nullptr), table(l), d.nv[l]);
+    if (x_dt)
+      for (int l = 0; l < D; ++l) jobs.add(sweep_args(l, *x_dt, nullptr), table(l), d.nv[l]);
     slmpp_status st = SLMPP_OK;
-    if (!field_valid) {
-      st = field(kick_dt);
-      if (kick_dt == 0.0) add_v_tables(jobs, kick_dt);
-    } else {
+    if (!field_valid)
+      st = field(&kick_dt);
+    else
       add_v_tables(jobs, kick_dt);
-    }
     return st == SLMPP_OK ? make_tables(jobs) : st;
   }
 };
@@ -1024,7 +1022,7 @@ slmpp_status slmpp_kick(slmpp_ctx* c, double dt) {
   if (!c) return SLMPP_ERR_INVALID;
   if (!std::isfinite(dt)) return c->fail(SLMPP_ERR_NONFINITE, "dt is not finite");
   if (dt == 0.0) return c->field_valid ? SLMPP_OK : c->field();
-  slmpp_status st = c->prepare(dt, 0.0);
+  slmpp_status st = c->prepare(dt, nullptr);
   if (st != SLMPP_OK) return st;
   c->field_valid = false;
   return c->kick(dt);
@@ -1111,15 +1109,14 @@ slmpp_status slmpp_step(slmpp_ctx* c, double dt, int32_t nsteps) {
   const bool merged = (c->d.flags & SLMPP_FLAG_MERGE_KICKS) != 0;
   const double half = 0.5 * dt;
   slmpp_status st = SLMPP_OK;
-  if (dt == 0.0) return c->field();  // nothing moves; a step ends with the field of f
-  st = c->prepare(half, dt);
+  st = c->prepare(half, &dt);
   if (st == SLMPP_OK) st = c->kick(half);
   for (int32_t it = 0; it < nsteps && st == SLMPP_OK; ++it) {
     bool fused = false;
     const bool last = it + 1 == nsteps;
     st = c->x_block(dt, &fused);
     const double next = merged && !last ? dt : half;
-    if (st == SLMPP_OK) st = c->field(next, fused);
+    if (st == SLMPP_OK) st = c->field(&next, fused);
     if (st == SLMPP_OK) st = c->kick(next, merged || last ? 1 : 2);
   }
   if (st != SLMPP_OK) c->field_valid = false;

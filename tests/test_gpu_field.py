@@ -113,3 +113,24 @@ def test_zero_time_step_keeps_f_and_leaves_the_field(S):
     assert np.abs(rho - O.density_moment(grid, f0)).max() <= 64 * EPS * rho.max()
     assert np.abs(acc - O.field(grid, f0)).max() <= 1e-12 * np.abs(acc).max()
     ctx.close()
+
+
+@pytest.mark.parametrize("time", ["sl", "rk3"])
+@pytest.mark.parametrize("D", [1, 2])
+def test_zero_time_step_runs_its_sweeps(S, D, time):
+    """A step of no duration is its sweeps all the same: a cell that is no
+    number makes the field, and with it every swept cell, no number; TVD-RK
+    combines its stages in floating point (a few ulp of the oracle's)."""
+    spec = dict(W.landau_run(D, 6, 16, 0.5, 0.3, 5), time=time)
+    print(f"case zero time step D={D} time={time}", flush=True)
+    f0 = W.random_field(spec["nx"][:D] + spec["nv"][:D], 3)
+    ctx = S.Context(S.make_desc(spec, 0))
+    ctx.init_f_host(f0)
+    ctx.step(0.0, 2)
+    f = ctx.get_f().reshape(f0.shape)
+    assert np.abs(f - f0).max() <= (0.0 if time == "sl" else 64 * EPS * f0.max())
+    f0.flat[5] = np.nan
+    ctx.init_f_host(f0)
+    ctx.step(0.0, 1)
+    assert np.isnan(ctx.get_f()).all()
+    ctx.close()
