@@ -251,7 +251,8 @@ slmpp_status slmpp_velocity_distribution(slmpp_ctx* ctx, double* F_dev);
  * Fourier transform with the Green function of order poisson_order
  * (Sec. 2.2), then accel_l = -d(phi)/dx_l by the FDA of the same order
  * (App. C).  phi_dev may be NULL.  rho_dev and accel_dev (D*prod(nx)) are
- * device arrays that must not overlap the workspace. */
+ * device arrays that must not overlap the workspace.  phi_dev or accel_dev
+ * may overlap rho_dev (the density is then overwritten). */
 slmpp_status slmpp_poisson_solve(slmpp_ctx* ctx, const double* rho_dev, double* phi_dev,
                                  double* accel_dev);
 

@@ -566,8 +566,16 @@ struct slmpp_ctx {
     const double part_bytes = 8.0 * (double)(nxs / d.nx[0]) * mom_sub * d.nx[0] + 8.0 * nxs;
     hipError_t e = hipSuccess;
     if (conv_field) {
-      // one launch; with row sums it is the moment's
+      // one launch; with row sums it is the moment's.  Its workgroups store
+      // phi and accel while others still read all of the density: a density
+      // that an output overlaps is copied first.
       e = part ? tic(2, part_bytes, 0.0) : tic(3, solve_bytes, 0.0);
+      auto overlaps = [&](const double* out) { return out < rho_dev + nxs && rho_dev < out + nxs; };
+      if (e == hipSuccess && !part && (overlaps(phi_dev) || overlaps(accel_dev))) {
+        double* copy = reinterpret_cast<double*>(bufA());
+        e = launch_to_double(SLMPP_F64, rho_dev, copy, nxs, stream);
+        rho_dev = copy;
+      }
       if (e == hipSuccess)
         e = launch_field_conv((int)nxs, part, (int)mom_sub, dvol, rho_dev, phi_dev, accel_dev, conv(),
                               d.storage, d.order, tabs, stream);
