@@ -170,12 +170,13 @@ template <typename T, int NT, bool GLOB>
 __global__ void __attribute__((amdgpu_flat_work_group_size(1, NT), amdgpu_waves_per_eu(4)))
 velocity_moments_kernel(const T* __restrict__ f, int D, int n1,
                                                               int n2, int n3, double3 vlo, double3 dv,
-                                                              double dvol, int64_t nxs,
+                                                              double dvol, int64_t nxs, int64_t cell0,
                                                               double* __restrict__ rho,
                                                               double* __restrict__ mean,
                                                               double* __restrict__ disp,
                                                               KSum* __restrict__ marg) {
   using V = typename UVec<T>::type;
+  const int64_t cell = cell0 + blockIdx.x;
   constexpr int VN = UVec<T>::N;
   constexpr int NW = NT / 64;
   constexpr int CH = 64 * VN * kMomVec;  // plane elements of a full chunk
@@ -190,7 +191,7 @@ velocity_moments_kernel(const T* __restrict__ f, int D, int n1,
   KSum* M2 = M1 + n1;
   KSum* M3 = M2 + n2;
   const int np = n2 * n3;
-  const T* b = f + (int64_t)blockIdx.x * n1 * np;
+  const T* b = f + cell * n1 * np;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   for (int k = tid; k < n1 + n2 + n3; k += NT) M1[k] = KSum{0.0, 0.0};
   __syncthreads();
@@ -373,9 +374,9 @@ velocity_moments_kernel(const T* __restrict__ f, int D, int n1,
     }
     const double m2 = wave_sum(s2);
     if (lane == 0) {
-      mean[(int64_t)ax * nxs + blockIdx.x] = u;
-      disp[(int64_t)ax * nxs + blockIdx.x] = m0 != 0.0 ? m2 / m0 : 0.0;
-      if (ax == 0) rho[blockIdx.x] = dvol * m0;
+      mean[(int64_t)ax * nxs + cell] = u;
+      disp[(int64_t)ax * nxs + cell] = m0 != 0.0 ? m2 / m0 : 0.0;
+      if (ax == 0) rho[cell] = dvol * m0;
     }
   }
 }
@@ -990,11 +991,13 @@ hipError_t launch_velocity_moments(int dtype, const void* f, int D, const int64_
     const int64_t ch = 64 * UVec<T>::N * kMomVec;
     const int64_t axes = n1 + n2 + n3;
     size_t lds = sizeof(double) * ((size_t)(NT / 64) * std::min<int64_t>(ch, (int64_t)n2 * n3) + std::max(NT, n3));
-    // axes of several thousand cells each: few spatial cells fit the GPU
-    // then, and the scratch holds their marginals
+    // axes of several thousand cells each: the scratch holds the marginals of
+    // as many spatial cells at a time as fit it
     KSum* marg = nullptr;
+    int64_t per = nxs;
     if (lds + sizeof(KSum) * axes > 160 * 1024) {
-      if (nxs * axes * 2 > scratch_doubles) return hipErrorInvalidValue;
+      per = std::min(nxs, scratch_doubles / (2 * axes));
+      if (per < 1) return hipErrorInvalidValue;
       marg = reinterpret_cast<KSum*>(scratch);
     } else {
       lds += sizeof(KSum) * axes;
@@ -1005,8 +1008,9 @@ hipError_t launch_velocity_moments(int dtype, const void* f, int D, const int64_
                                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
       if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(kern, dim3((unsigned)nxs), dim3(NT), lds, s, (const T*)f, D, n1, n2, n3, lo3,
-                       dv3, dvol, nxs, rho, mean, disp, marg);
+    for (int64_t cell0 = 0; cell0 < nxs; cell0 += per)
+      hipLaunchKernelGGL(kern, dim3((unsigned)std::min(per, nxs - cell0)), dim3(NT), lds, s, (const T*)f, D,
+                         n1, n2, n3, lo3, dv3, dvol, nxs, cell0, rho, mean, disp, marg);
     return hipGetLastError();
   };
   // one wavefront per spatial cell where there are enough cells to fill the
