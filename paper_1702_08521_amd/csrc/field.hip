@@ -146,8 +146,8 @@ __device__ __forceinline__ typename UVec<T>::type load_part(const T* p, int64_t 
 
 // Velocity moments of one spatial cell per workgroup (Sec. 2.3): density,
 // mean velocity and dispersion per velocity axis, from one read of the
-// cell's velocity block.  The block [n1][n2][n3] (n1 = 1 for one velocity
-// axis, n3 = 1 for two) is summed to its marginals M_l(j_l) in LDS, and mean
+// cell's velocity block.  The block [n1][n2][n3] (n3 = 1 for two velocity
+// axes) is summed to its marginals M_l(j_l) in LDS, and mean
 // and dispersion of axis l come from M_l alone (two passes over n_l numbers,
 // so nothing cancels that did not cancel in two passes over f).
 //
@@ -348,8 +348,8 @@ velocity_moments_kernel(const T* __restrict__ f, int D, int n1,
   __syncthreads();
   // density, then mean and dispersion per axis, axes dealt to the wavefronts
   for (int ax = wave; ax < D; ax += NW) {
-    const KSum* M = D == 3 ? (ax == 0 ? M1 : ax == 1 ? M2 : M3) : (D == 2 ? (ax == 0 ? M1 : M2) : M2);
-    const int n = D == 3 ? (ax == 0 ? n1 : ax == 1 ? n2 : n3) : (D == 2 ? (ax == 0 ? n1 : n2) : n2);
+    const KSum* M = ax == 0 ? M1 : ax == 1 ? M2 : M3;
+    const int n = ax == 0 ? n1 : ax == 1 ? n2 : n3;
     const double lo = ax == 0 ? vlo.x : ax == 1 ? vlo.y : vlo.z;
     const double h = ax == 0 ? dv.x : ax == 1 ? dv.y : dv.z;
     auto wave_sum = [&](KSum v) {
@@ -379,6 +379,111 @@ velocity_moments_kernel(const T* __restrict__ f, int D, int n1,
       if (ax == 0) rho[cell] = dvol * m0;
     }
   }
+}
+
+// The same for one velocity axis and for small velocity blocks: two passes over
+// the cell's contiguous velocity block (the second re-reads it from cache);
+// compensated double sums of plain sums over groups of eight elements.  Bound
+// by the latency of the passes, or on large blocks by the arithmetic of every
+// element, which the marginals save.
+template <typename T, int NT, int D>  // D: velocity axes (a constant: the loops over
+                                      // axes unroll and every accumulator stays in registers)
+__global__ void __launch_bounds__(NT) velocity_moments_direct_kernel(const T* __restrict__ f,
+                                                              int64_t nvs, int3 nv, double3 vlo,
+                                                              double3 dv, double dvol, int64_t nxs,
+                                                              double* __restrict__ rho,
+                                                              double* __restrict__ mean,
+                                                              double* __restrict__ disp) {
+  const T* b = f + (int64_t)blockIdx.x * nvs;
+  const int n[3] = {nv.x, nv.y, nv.z};
+  const double lo[3] = {vlo.x, vlo.y, vlo.z}, h[3] = {dv.x, dv.y, dv.z};
+  // velocity index of element k as digits (last axis fastest): the digits
+  // of this thread's first element and of the stride NT, then a digit-wise
+  // add with carries per step instead of a division per element
+  int j0[3] = {0, 0, 0}, st[3] = {0, 0, 0};
+  {
+    int64_t rem = threadIdx.x, str = NT;
+    for (int l = D - 1; l >= 0; --l) {
+      j0[l] = (int)(rem % n[l]);
+      rem /= n[l];
+      st[l] = (int)(str % n[l]);
+      str /= n[l];
+    }
+  }
+  int j[3];
+  auto restart = [&]() {
+    for (int l = 0; l < 3; ++l) j[l] = j0[l];
+  };
+  auto centres = [&](double* v) {
+    for (int l = 0; l < D; ++l) v[l] = lo[l] + ((double)j[l] + 0.5) * h[l];
+  };
+  auto next = [&]() {  // j += st; past the last element the digits are unused
+    int carry = 0;
+    for (int l = D - 1; l >= 0; --l) {
+      j[l] += st[l] + carry;
+      carry = j[l] >= n[l];
+      if (carry) j[l] -= n[l];
+    }
+  };
+  // each thread adds groups of up to kGroup of its elements plainly and
+  // feeds the group sums to the compensated accumulators
+  constexpr int kGroup = 8;
+  KSum s0{0.0, 0.0}, s1[3] = {{0.0, 0.0}, {0.0, 0.0}, {0.0, 0.0}};
+  double p0 = 0.0, p1[3] = {0.0, 0.0, 0.0};
+  int cnt = 0;
+  restart();
+  for (int64_t k = threadIdx.x; k < nvs; k += NT, next()) {
+    double v[3];
+    centres(v);
+    const double x = (double)b[k];
+    p0 += x;
+    for (int l = 0; l < D; ++l) p1[l] += x * v[l];
+    if (++cnt == kGroup) {
+      kadd(s0, p0);
+      for (int l = 0; l < D; ++l) kadd(s1[l], p1[l]);
+      p0 = 0.0;
+      for (int l = 0; l < D; ++l) p1[l] = 0.0;
+      cnt = 0;
+    }
+  }
+  kadd(s0, p0);
+  for (int l = 0; l < D; ++l) kadd(s1[l], p1[l]);
+  const KSum t0 = block_ksum<NT>(s0);
+  const double m0 = t0.s + t0.c;
+  double u[3] = {0.0, 0.0, 0.0};
+  for (int l = 0; l < D; ++l) {
+    const KSum t1 = block_ksum<NT>(s1[l]);
+    u[l] = m0 != 0.0 ? (t1.s + t1.c) / m0 : 0.0;
+  }
+  KSum s2[3] = {{0.0, 0.0}, {0.0, 0.0}, {0.0, 0.0}};
+  double p2[3] = {0.0, 0.0, 0.0};
+  cnt = 0;
+  restart();
+  for (int64_t k = threadIdx.x; k < nvs; k += NT, next()) {
+    double v[3];
+    centres(v);
+    const double x = (double)b[k];
+    for (int l = 0; l < D; ++l) {
+      const double d = v[l] - u[l];
+      p2[l] += x * d * d;
+    }
+    if (++cnt == kGroup) {
+      for (int l = 0; l < D; ++l) {
+        kadd(s2[l], p2[l]);
+        p2[l] = 0.0;
+      }
+      cnt = 0;
+    }
+  }
+  for (int l = 0; l < D; ++l) kadd(s2[l], p2[l]);
+  for (int l = 0; l < D; ++l) {
+    const KSum t2 = block_ksum<NT>(s2[l]);
+    if (threadIdx.x == 0) {
+      mean[(int64_t)l * nxs + blockIdx.x] = u[l];
+      disp[(int64_t)l * nxs + blockIdx.x] = m0 != 0.0 ? (t2.s + t2.c) / m0 : 0.0;
+    }
+  }
+  if (threadIdx.x == 0) rho[blockIdx.x] = dvol * m0;
 }
 
 // F[k] = xvol * sum_x f[x][k]: a thread walks the spatial cells of its
@@ -973,18 +1078,59 @@ hipError_t launch_copy(void* dst, const void* src, size_t bytes, hipStream_t s) 
   return hipGetLastError();
 }
 
+namespace {
+// spatial cells from which one wavefront each takes the marginals
+constexpr int64_t kMomMany = 2048;
+// Whether the moments of a velocity block [n1][plane] are taken directly rather
+// than through the marginals, whose folds and barriers cost more than they save
+// where there is little to add up.  us, directly / through the marginals:
+//   one axis (a plane of one element each): 1024 x 4096 FP32 11 / 850;
+//   two axes, few cells: 17^2 x 54x61 11 / 32, 8^2 x 128^2 FP64 29 / 31, 4^2 x
+// 200x210 63 / 41; many: 142^2 x 54x61 FP32 167 / 205, FP64 218 / 177, 64^2 x
+// 128^2 138 / 105;
+//   three axes, few cells: 12^3 x 8^3 16 / 27, 8^3 x 12^3 FP64 12 / 9; many: 37^3 x
+// 9x11x13 329 / 290;
+//   few large planes (a fold after each few): 5^3 x 4x40x40 18 / 30, 129^2 x
+// 2x2000 161 / 5245; small planes (many lanes' sums each): 129^2 x 2000x2 162 / 566.
+bool moments_direct(bool f64, int D, int64_t nxs, int n1, int64_t plane) {
+  const bool many = nxs >= kMomMany;
+  const int64_t nvs = n1 * plane;
+  if (D == 1 || plane < 32 || (plane >= 256 && n1 < (many ? 4 : 8))) return true;
+  if (D == 2) return nvs < (!many ? 16384 : f64 ? 2048 : 9216);
+  return !many && nvs < (f64 ? 768 : 2048);
+}
+}  // namespace
+
 hipError_t launch_velocity_moments(int dtype, const void* f, int D, const int64_t* nv,
                                    const double* vlo, const double* dv, int64_t nxs,
                                    double* rho, double* mean, double* disp, double* scratch,
                                    int64_t scratch_doubles, hipStream_t s) {
   if (D < 1 || D > 3) return hipErrorInvalidValue;
   double dvol = 1.0;
-  for (int l = 0; l < D; ++l) dvol *= dv[l];
-  // the kernel's [n1][n2][n3]: one velocity axis is its n2, two are n1 and n2
-  const int n1 = D == 1 ? 1 : (int)nv[0], n2 = D == 1 ? (int)nv[0] : (int)nv[1];
-  const int n3 = D == 3 ? (int)nv[2] : 1;
+  int64_t nvs = 1;
+  for (int l = 0; l < D; ++l) {
+    dvol *= dv[l];
+    nvs *= nv[l];
+  }
+  const int n1 = (int)nv[0], n2 = D > 1 ? (int)nv[1] : 1, n3 = D > 2 ? (int)nv[2] : 1;
   const double3 lo3 = make_double3(vlo[0], D > 1 ? vlo[1] : 0.0, D > 2 ? vlo[2] : 0.0);
   const double3 dv3 = make_double3(dv[0], D > 1 ? dv[1] : 1.0, D > 2 ? dv[2] : 1.0);
+  if (moments_direct(dtype == SLMPP_F64, D, nxs, n1, (int64_t)n2 * n3)) {
+    auto direct = [&](auto tag, auto axes) {
+      using T = decltype(tag);
+      constexpr int NT = 256;
+      hipLaunchKernelGGL((velocity_moments_direct_kernel<T, NT, decltype(axes)::value>), dim3((unsigned)nxs),
+                         dim3(NT), 0, s, (const T*)f, nvs, make_int3(n1, n2, n3), lo3, dv3, dvol, nxs, rho,
+                         mean, disp);
+      return hipGetLastError();
+    };
+    auto axes = [&](auto tag) {
+      return D == 1   ? direct(tag, std::integral_constant<int, 1>{})
+             : D == 2 ? direct(tag, std::integral_constant<int, 2>{})
+                      : direct(tag, std::integral_constant<int, 3>{});
+    };
+    return dtype == SLMPP_F64 ? axes(0.0) : axes(0.0f);
+  }
   auto go = [&](auto tag, auto width) -> hipError_t {
     using T = decltype(tag);
     constexpr int NT = decltype(width)::value;
@@ -1018,7 +1164,7 @@ hipError_t launch_velocity_moments(int dtype, const void* f, int D, const int64_
   // where there are not
   using One = std::integral_constant<int, 64>;
   using Four = std::integral_constant<int, 256>;
-  if (nxs >= 2048) return dtype == SLMPP_F64 ? go(0.0, One{}) : go(0.0f, One{});
+  if (nxs >= kMomMany) return dtype == SLMPP_F64 ? go(0.0, One{}) : go(0.0f, One{});
   return dtype == SLMPP_F64 ? go(0.0, Four{}) : go(0.0f, Four{});
 }
 
