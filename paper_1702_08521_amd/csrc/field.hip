@@ -116,6 +116,38 @@ __device__ __forceinline__ void kmerge2(KSum& a, const KSum& b) {
   kadd2(a, b.s);
   a.c += b.c;
 }
+__device__ __forceinline__ KSum shfl_ksum(const KSum& v, int off) {
+  return {__shfl_xor(v.s, off, 64), __shfl_xor(v.c, off, 64)};
+}
+// Sum over each row of 16 lanes, in all of them: pairs by data-parallel
+// permutes of the row (mirrored, its halves mirrored, its quads reversed, its
+// pairs swapped), which take a few cycles where a shuffle goes through the LDS.
+template <int CTRL>
+__device__ __forceinline__ double dpp(double v) {
+  const int64_t b = __double_as_longlong(v);
+  const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, 0xf, 0xf, true);
+  const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), CTRL, 0xf, 0xf, true);
+  return __longlong_as_double((int64_t)(((uint64_t)hi << 32) | lo));
+}
+template <int CTRL>
+__device__ __forceinline__ void merge_dpp(KSum& v) {
+  const KSum o{dpp<CTRL>(v.s), dpp<CTRL>(v.c)};
+  kmerge2(v, o);
+}
+constexpr int kRowMirror = 0x140, kHalfMirror = 0x141, kQuadReverse = 0x1b, kPairSwap = 0xb1;
+__device__ __forceinline__ void sum_rows(KSum& v) {
+  merge_dpp<kRowMirror>(v);
+  merge_dpp<kHalfMirror>(v);
+  merge_dpp<kQuadReverse>(v);
+  merge_dpp<kPairSwap>(v);
+}
+__device__ __forceinline__ double sum_rows(double v) {
+  v += dpp<kRowMirror>(v);
+  v += dpp<kHalfMirror>(v);
+  v += dpp<kQuadReverse>(v);
+  v += dpp<kPairSwap>(v);
+  return v;
+}
 
 // 16-byte vectors at element-aligned addresses (the hardware takes global
 // vector accesses at any 4-byte address)
@@ -159,8 +191,9 @@ __device__ __forceinline__ typename UVec<T>::type load_part(const T* p, int64_t 
 // wavefront, is taken several j1 at a time) and kMomPlanes planes per burst
 // of loads: the plane sums go to M_1(j1), and the lanes' running sums over j1
 // give the marginal over (j2, j3) of the chunk, which is folded into M_2 and
-// M_3.  Sums over more than a few values are compensated.  Held to 128
-// VGPRs: at three wavefronts per SIMD instead of four it took 958 us; four
+// M_3.  A lane adds at most eight values plainly; every sum above that is a
+// compensated pair (plain sums took 822 us of 24^3 x 40^3 FP32, these 942).
+// Held to 128 VGPRs: at three wavefronts per SIMD instead of four it took 958 us; four
 // vectors per lane and two planes per burst 970 us, the wavefronts of a
 // workgroup sharing one spatial cell 1118 us.
 // GLOB: the marginals in `marg` instead of LDS (axes too long for it).
@@ -185,8 +218,8 @@ velocity_moments_kernel(const T* __restrict__ f, int D, int n1,
   // parts of M_3 of that chunk, and the marginals M_l
   const int cl = min(CH, n2 * n3);
   double* W = reinterpret_cast<double*>(mom_smem);
-  double* Q = W + NW * cl;
-  KSum* M1 = reinterpret_cast<KSum*>(Q + max(NT, n3));
+  KSum* Q = reinterpret_cast<KSum*>(W + NW * cl);
+  KSum* M1 = Q + max(NT, n3);
   if constexpr (GLOB) M1 = marg + (int64_t)blockIdx.x * (n1 + n2 + n3);
   KSum* M2 = M1 + n1;
   KSum* M3 = M2 + n2;
@@ -269,21 +302,27 @@ velocity_moments_kernel(const T* __restrict__ f, int D, int n1,
         // four sums at once: halves of the wavefront swap pairs, quarters
         // single sums, and 16 lanes add up one plane each
         const bool h = lane & 32, q = lane & 16;
-        double u0 = h ? rs[2] : rs[0], u1 = h ? rs[3] : rs[1];
-        u0 += __shfl_xor(h ? rs[0] : rs[2], 32, 64);
-        u1 += __shfl_xor(h ? rs[1] : rs[3], 32, 64);
-        double u = q ? u1 : u0;
-        u += __shfl_xor(q ? u0 : u1, 16, 64);
-#pragma unroll
-        for (int off = 8; off > 0; off >>= 1) u += __shfl_xor(u, off, 64);
+        KSum u0{h ? rs[2] : rs[0], 0.0}, u1{h ? rs[3] : rs[1], 0.0};
+        kadd2(u0, __shfl_xor(h ? rs[0] : rs[2], 32, 64));
+        kadd2(u1, __shfl_xor(h ? rs[1] : rs[3], 32, 64));
+        KSum u = q ? u1 : u0;
+        const KSum o = shfl_ksum(q ? u0 : u1, 16);
+        kmerge2(u, o);
+        sum_rows(u);
         const int j1 = j0 + ((h ? 2 : 0) + (q ? 1 : 0)) * NW;
-        if ((lane & 15) == 0 && j1 < n1) kadd2(M1[j1], u);
+        if ((lane & 15) == 0 && j1 < n1) kmerge2(M1[j1], u);
       } else {
 #pragma unroll
         for (int g = 0; g < kMomPlanes; ++g) {
-          for (int off = 1; off < lpp; off <<= 1) rs[g] += __shfl_xor(rs[g], off, 64);
+          KSum u{rs[g], 0.0};
+          if (lpp >= 16) {
+            sum_rows(u);
+            for (int off = 16; off < lpp; off <<= 1) kmerge2(u, shfl_ksum(u, off));
+          } else {
+            for (int off = 1; off < lpp; off <<= 1) kmerge2(u, shfl_ksum(u, off));
+          }
           const int j1 = j0 + g * NW * sub;
-          if (pl == 0 && j1 < n1) kadd2(M1[j1], rs[g]);
+          if (pl == 0 && j1 < n1) kmerge2(M1[j1], u);
         }
       }
     }
@@ -292,85 +331,107 @@ velocity_moments_kernel(const T* __restrict__ f, int D, int n1,
 #pragma unroll
       for (int k = 0; k < kMomVec; ++k)
 #pragma unroll
-        for (int c = 0; c < VN; ++c) {
-          const KSum o{__shfl_xor(acc[k][c].s, off, 64), __shfl_xor(acc[k][c].c, off, 64)};
-          kmerge2(acc[k][c], o);
-        }
+        for (int c = 0; c < VN; ++c) kmerge2(acc[k][c], shfl_ksum(acc[k][c], off));
     const int ce = min(CH, np - c0);
-    if (sl == 0) {
+    const int r0 = c0 / n3, rows = (c0 + ce - 1) / n3 - r0 + 1;
+    const int parts = n3 < NT ? NT / n3 : 1;
+    auto to_lds = [&](auto&& value) {  // the wavefronts' marginals of the chunk
+      if (sl == 0) {
 #pragma unroll
-      for (int k = 0; k < kMomVec; ++k)
+        for (int k = 0; k < kMomVec; ++k)
 #pragma unroll
-        for (int c = 0; c < VN; ++c) {
-          const int e = (pl + k * lpp) * VN + c;
-          if (e < ce) W[wave * cl + e] = acc[k][c].s + acc[k][c].c;
-        }
-    }
-    __syncthreads();
-    auto P = [&](int e) {  // marginal at plane element c0 + e
-      double v = W[e];
-#pragma unroll
-      for (int w = 1; w < NW; ++w) v += W[w * cl + e];
-      return v;
+          for (int c = 0; c < VN; ++c) {
+            const int e = (pl + k * lpp) * VN + c;
+            if (e < ce) W[wave * cl + e] = value(acc[k][c]);
+          }
+      }
+      __syncthreads();
     };
     // M_2: 16 lanes per row of the chunk; M_3: the rows dealt to as many
-    // parts as there are threads for, then the parts in order
-    const int r0 = c0 / n3, rows = (c0 + ce - 1) / n3 - r0 + 1;
-    for (int q = tid / 16; q < (rows + NT / 16 - 1) / (NT / 16) * (NT / 16); q += NT / 16) {
-      double v = 0.0;
-      if (q < rows) {
-        const int lo = max((r0 + q) * n3, c0) - c0, hi = min((r0 + q + 1) * n3, c0 + ce) - c0;
-        KSum m{0.0, 0.0};
-        for (int e = lo + (tid & 15); e < hi; e += 16) kadd2(m, P(e));
-        v = m.s + m.c;
-      }
+    // parts as there are threads for, then the parts in order.  First the
+    // sums, compensated, then their errors, plainly into the errors.
+    const int rows16 = (rows + NT / 16 - 1) / (NT / 16) * (NT / 16);
+    auto row_lo = [&](int q) { return max((r0 + q) * n3, c0) - c0; };
+    auto row_hi = [&](int q) { return min((r0 + q + 1) * n3, c0 + ce) - c0; };
+    to_lds([](const KSum& v) { return v.s; });
+    for (int q = tid / 16; q < rows16; q += NT / 16) {
+      KSum m{0.0, 0.0};
+      if (q < rows)
+        for (int e = row_lo(q) + (tid & 15); e < row_hi(q); e += 16)
 #pragma unroll
-      for (int off = 1; off < 16; off <<= 1) v += __shfl_xor(v, off, 64);
-      if ((tid & 15) == 0 && q < rows) kadd2(M2[r0 + q], v);
+          for (int w = 0; w < NW; ++w) kadd2(m, W[w * cl + e]);
+      sum_rows(m);
+      if ((tid & 15) == 0 && q < rows) kmerge2(M2[r0 + q], m);
     }
-    const int parts = n3 < NT ? NT / n3 : 1;
     for (int j = tid; j < parts * n3; j += NT) {
       const int j3 = j % n3;
       KSum m{0.0, 0.0};
       for (int r = r0 + j / n3; r < r0 + rows; r += parts) {
         const int e = r * n3 + j3 - c0;
-        if (e >= 0 && e < ce) kadd2(m, P(e));
+        if (e >= 0 && e < ce)
+#pragma unroll
+          for (int w = 0; w < NW; ++w) kadd2(m, W[w * cl + e]);
       }
-      Q[j] = m.s + m.c;
+      Q[j] = m;
+    }
+    __syncthreads();
+    to_lds([](const KSum& v) { return v.c; });
+    for (int q = tid / 16; q < rows16; q += NT / 16) {
+      double v = 0.0;
+      if (q < rows)
+        for (int e = row_lo(q) + (tid & 15); e < row_hi(q); e += 16)
+#pragma unroll
+          for (int w = 0; w < NW; ++w) v += W[w * cl + e];
+      v = sum_rows(v);
+      if ((tid & 15) == 0 && q < rows) M2[r0 + q].c += v;
+    }
+    for (int j = tid; j < parts * n3; j += NT) {
+      const int j3 = j % n3;
+      double v = 0.0;
+      for (int r = r0 + j / n3; r < r0 + rows; r += parts) {
+        const int e = r * n3 + j3 - c0;
+        if (e >= 0 && e < ce)
+#pragma unroll
+          for (int w = 0; w < NW; ++w) v += W[w * cl + e];
+      }
+      Q[j].c += v;
     }
     __syncthreads();
     for (int j3 = tid; j3 < n3; j3 += NT) {
       KSum m = M3[j3];
-      for (int q = 0; q < parts; ++q) kadd2(m, Q[q * n3 + j3]);
+      for (int q = 0; q < parts; ++q) kmerge2(m, Q[q * n3 + j3]);
       M3[j3] = m;
     }
   }
   __syncthreads();
-  // density, then mean and dispersion per axis, axes dealt to the wavefronts
+  // density, then mean and dispersion per axis, axes dealt to the wavefronts;
+  // one density for all of them
+  auto marginal = [&](int ax) { return ax == 0 ? M1 : ax == 1 ? M2 : M3; };
+  auto cells_of = [&](int ax) { return ax == 0 ? n1 : ax == 1 ? n2 : n3; };
+  auto wave_sum = [&](KSum v) {
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) kmerge2(v, shfl_ksum(v, off));
+    return __shfl(v.s + v.c, 0, 64);
+  };
+  KSum s0{0.0, 0.0};
+  for (int j = lane; j < cells_of(0); j += 64) kmerge2(s0, marginal(0)[j]);
+  const double m0 = wave_sum(s0);
   for (int ax = wave; ax < D; ax += NW) {
-    const KSum* M = ax == 0 ? M1 : ax == 1 ? M2 : M3;
-    const int n = ax == 0 ? n1 : ax == 1 ? n2 : n3;
+    const KSum* M = marginal(ax);
+    const int n = cells_of(ax);
     const double lo = ax == 0 ? vlo.x : ax == 1 ? vlo.y : vlo.z;
     const double h = ax == 0 ? dv.x : ax == 1 ? dv.y : dv.z;
-    auto wave_sum = [&](KSum v) {
-#pragma unroll
-      for (int off = 1; off < 64; off <<= 1) {
-        const KSum o{__shfl_xor(v.s, off, 64), __shfl_xor(v.c, off, 64)};
-        kmerge2(v, o);
-      }
-      return v.s + v.c;
-    };
-    KSum s0{0.0, 0.0}, s1{0.0, 0.0}, s2{0.0, 0.0};
+    KSum s1{0.0, 0.0}, s2{0.0, 0.0};
     for (int j = lane; j < n; j += 64) {
-      const double m = M[j].s + M[j].c;
-      kadd2(s0, m);
-      kadd2(s1, m * (lo + ((double)j + 0.5) * h));
+      const double v = lo + ((double)j + 0.5) * h;
+      kadd2(s1, M[j].s * v);
+      s1.c += M[j].c * v;
     }
-    const double m0 = wave_sum(s0), m1 = wave_sum(s1);
-    const double u = m0 != 0.0 ? m1 / m0 : 0.0;
+    const double u = m0 != 0.0 ? wave_sum(s1) / m0 : 0.0;
     for (int j = lane; j < n; j += 64) {
       const double d = lo + ((double)j + 0.5) * h - u;
-      kadd2(s2, (M[j].s + M[j].c) * d * d);
+      kadd2(s2, M[j].s * d * d);
+      s2.c += M[j].c * d * d;
     }
     const double m2 = wave_sum(s2);
     if (lane == 0) {
@@ -1136,7 +1197,8 @@ hipError_t launch_velocity_moments(int dtype, const void* f, int D, const int64_
     constexpr int NT = decltype(width)::value;
     const int64_t ch = 64 * UVec<T>::N * kMomVec;
     const int64_t axes = n1 + n2 + n3;
-    size_t lds = sizeof(double) * ((size_t)(NT / 64) * std::min<int64_t>(ch, (int64_t)n2 * n3) + std::max(NT, n3));
+    size_t lds = sizeof(double) * (size_t)(NT / 64) * std::min<int64_t>(ch, (int64_t)n2 * n3) +
+                 sizeof(KSum) * std::max(NT, n3);
     // axes of several thousand cells each: the scratch holds the marginals of
     // as many spatial cells at a time as fit it
     KSum* marg = nullptr;
