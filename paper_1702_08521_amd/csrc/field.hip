@@ -834,12 +834,8 @@ __global__ void __launch_bounds__(NT) diag_f_kernel(const T* __restrict__ f, int
       for (int c = 0; c < VN; ++c) one(x[c]);
       return;
     }
-    if constexpr (VN == 4) {
-      kadd2(acc, t);  // four floats: exact in double to its last bits
-    } else {
 #pragma unroll
-      for (int c = 0; c < VN; ++c) kadd2(acc, (double)x[c]);
-    }
+    for (int c = 0; c < VN; ++c) kadd2(acc, (double)x[c]);
 #pragma unroll
     for (int c = 0; c < VN; ++c) {
       mn = x[c] < mn ? x[c] : mn;

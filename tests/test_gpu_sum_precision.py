@@ -1,11 +1,12 @@
-"""Sums over the velocity cells hold a compensated pair above small
+"""Sums over the velocity cells and over f hold a compensated pair above small
 groups: two cells +-2^60 among ones must cancel without taking the ones along.
 
 At most eight cells are added plainly before a compensated addition, so each of
 the two cells costs at most the seven ones beside it; everything else is exact
 (cells of unit volume): densities to 14, a mean velocity along an axis on which
 the two cells agree to 14 times the largest velocity over the number of cells
-for the numerator and as much for the denominator."""
+for the numerator and as much for the denominator.  The diagnostics compensate
+every value and are exact."""
 import numpy as np
 import pytest
 
@@ -68,4 +69,17 @@ def test_velocity_moments(S, bi, storage):
         ref = (ones * v).sum() / n
         got = mean.cpu().numpy()[axis * nxs:(axis + 1) * nxs]
         assert np.abs(got - ref).max() <= 2 * 14 * nv[axis] / (n - 14)
+    ctx.close()
+
+
+@pytest.mark.parametrize("storage", [0, 1])
+def test_diagnostics(S, storage):
+    ctx = S.Context(S.make_desc(_spec([7, 9], [30, 31]), storage))
+    ctx.field()
+    ctx.f.fill_(1.0)
+    flat = ctx.f.view(-1)
+    flat[10001] = BIG
+    flat[41234] = -BIG
+    print(f"case diagnostics storage={storage}", flush=True)
+    assert ctx.diag()["mass"] == flat.numel() - 2
     ctx.close()
