@@ -82,7 +82,8 @@ Layout layout_of(const slmpp_grid_desc& d) {
   // pencils per tile; down to 4 in one dimension)
   L.mom_doubles = d.D == 1 ? std::min<int64_t>(ncell, kConvRowSums)
                            : std::max<int64_t>(ncell / 64, std::min<int64_t>(ncell / 8, (int64_t)1 << 20));
-  L.mom = take(sizeof(double) * std::max<int64_t>(L.mom_doubles, 1));
+  // (pairs, from line_sweep_kernel)
+  L.mom = take(2 * sizeof(double) * std::max<int64_t>(L.mom_doubles, 1));
   // TVD-RK time integration keeps f^n of a sweep
   L.rkbuf = take((d.flags & SLMPP_FLAG_RK3) ? (size_t)ncell * (d.storage == SLMPP_F64 ? 8 : 4) : 0);
   // isolated boundaries: two complex buffers and the Green transform on the
@@ -267,6 +268,7 @@ struct slmpp_ctx {
   void* rkbuf() { return work + lay.rkbuf; }
   bool rk = false;  // SLMPP_FLAG_RK3
   int64_t mom_sub = 1;  // tiles per velocity block of the last fused x_1 sweep
+  bool mom_pairs = false;  // whether it left pairs
   size_t esize() const { return d.storage == SLMPP_F64 ? 8 : 4; }
 
   slmpp_status fail(slmpp_status code, const char* fmt, ...) {
@@ -417,6 +419,7 @@ struct slmpp_ctx {
         if (lp.lds_bytes && lp.tiles * (int64_t)s.n <= lay.mom_doubles) {
           s.mom = mom();
           mom_sub = lp.tpb;
+          mom_pairs = true;
           if (fused) *fused = true;
         } else {
           lp = LinePlan{};
@@ -428,6 +431,7 @@ struct slmpp_ctx {
         nvs % p.W == 0 && p.tiles * (int64_t)s.n <= lay.mom_doubles) {
       s.mom = mom();
       mom_sub = nvs / p.W;
+      mom_pairs = false;
       if (fused) *fused = true;
     }
     if (lp.lds_bytes && lp.K > 0 && !rk && reps > 1) {
@@ -563,6 +567,7 @@ struct slmpp_ctx {
     if (!phi_dev) phi_dev = phi();
     if (with_tables) *with_tables = conv_field || fplan.ok;
     const double solve_bytes = 8.0 * nxs * (2 + D);
+    // (the sums; not the errors kept with them)
     const double part_bytes = 8.0 * (double)(nxs / d.nx[0]) * mom_sub * d.nx[0] + 8.0 * nxs;
     hipError_t e = hipSuccess;
     if (conv_field) {
@@ -577,7 +582,7 @@ struct slmpp_ctx {
         rho_dev = copy;
       }
       if (e == hipSuccess)
-        e = launch_field_conv((int)nxs, part, (int)mom_sub, dvol, rho_dev, phi_dev, accel_dev, conv(),
+        e = launch_field_conv((int)nxs, part, mom_pairs, (int)mom_sub, dvol, rho_dev, phi_dev, accel_dev, conv(),
                               d.storage, d.order, tabs, stream);
       if (e == hipSuccess) e = toc();
       return e == hipSuccess ? SLMPP_OK : hip_fail(e, "field launch");
@@ -588,7 +593,7 @@ struct slmpp_ctx {
       const double2* t = isolated ? tw2() : tw();
       if (part) e = tic(2, part_bytes, 0.0);
       else e = tic(3, solve_bytes, 0.0);
-      if (e == hipSuccess) e = launch_field_forward(fplan, part, (int)mom_sub, dvol, rho_dev, A, t, stream);
+      if (e == hipSuccess) e = launch_field_forward(fplan, part, mom_pairs, (int)mom_sub, dvol, rho_dev, A, t, stream);
       if (part && e == hipSuccess) e = toc();
       if (part && e == hipSuccess) e = tic(3, solve_bytes, 0.0);
       if (e == hipSuccess)
@@ -600,7 +605,7 @@ struct slmpp_ctx {
     if (part) {
       const int n = (int)d.nx[0];
       e = tic(2, part_bytes, 0.0);
-      if (e == hipSuccess) e = launch_moment_reduce(part, n, nxs / n, mom_sub, dvol, rho_dev, stream);
+      if (e == hipSuccess) e = launch_moment_reduce(part, mom_pairs, n, nxs / n, mom_sub, dvol, rho_dev, stream);
       if (e == hipSuccess) e = toc();
     }
     if (e == hipSuccess) e = tic(3, solve_bytes, 0.0);

@@ -612,22 +612,32 @@ __global__ void __launch_bounds__(256) distribution_sum_kernel(const KSum* __res
 
 // rho[i * ncol + c] = dvol * sum_q part[(c * nsub + q) * n + i]; thread
 // (c, i) adds the nsub tile-row sums of its cell in tile order (compensated).
-__global__ void __launch_bounds__(256) moment_reduce_kernel(const double* __restrict__ part, int n,
+__global__ void __launch_bounds__(256) moment_reduce_kernel(const double* __restrict__ part,
+                                                            bool pairs, int n,
                                                             int64_t ncol, int64_t nsub, double dvol,
                                                             double* __restrict__ rho) {
   const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (g >= ncol * n) return;
   const int64_t c = g / n;
   const int i = (int)(g - c * n);
-  const double* p = part + c * nsub * n + i;
+  const int64_t at = c * nsub * n + i;
+  auto get = [&](int64_t q) {
+    return pairs ? reinterpret_cast<const double2*>(part)[at + q * n] : make_double2(part[at + q * n], 0.0);
+  };
   KSum acc0{0.0, 0.0}, acc1{0.0, 0.0};
   int64_t q = 0;
   for (; q + 1 < nsub; q += 2) {
-    const double x0 = p[q * n], x1 = p[(q + 1) * n];
-    kadd(acc0, x0);
-    kadd(acc1, x1);
+    const double2 x0 = get(q), x1 = get(q + 1);
+    kadd(acc0, x0.x);
+    kadd(acc1, x1.x);
+    acc0.c += x0.y;
+    acc1.c += x1.y;
   }
-  if (q < nsub) kadd(acc0, p[q * n]);
+  if (q < nsub) {
+    const double2 x0 = get(q);
+    kadd(acc0, x0.x);
+    acc0.c += x0.y;
+  }
   kmerge(acc0, acc1);
   rho[(int64_t)i * ncol + c] = dvol * (acc0.s + acc0.c);
 }
@@ -979,12 +989,12 @@ hipError_t launch_moment(int dtype, const void* f, int64_t nxs, int64_t nvs, dou
   return hipGetLastError();
 }
 
-hipError_t launch_moment_reduce(const double* part, int n, int64_t ncol, int64_t nsub, double dvol,
-                                double* rho, hipStream_t s) {
+hipError_t launch_moment_reduce(const double* part, bool pairs, int n, int64_t ncol, int64_t nsub,
+                                double dvol, double* rho, hipStream_t s) {
   const int64_t total = ncol * n;
   if (total <= 0) return hipSuccess;
   hipLaunchKernelGGL(moment_reduce_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s,
-                     part, n, ncol, nsub, dvol, rho);
+                     part, pairs, n, ncol, nsub, dvol, rho);
   return hipGetLastError();
 }
 

@@ -27,14 +27,39 @@
 namespace slmpp {
 namespace {
 
-struct KSum {
-  double s, c;
-};
-__device__ __forceinline__ void kadd(KSum& a, double x) {
-  const double t = a.s + x;
-  const double b = t - a.s;
-  a.c += (a.s - (t - b)) + (x - b);
-  a.s = t;
+// The density of cell i from its nsub row sums, part[s n + i] (pairs: each the
+// sum and its error), added in tile order.
+__device__ __forceinline__ double sum_rows(const double* part, bool pairs, int64_t i, int nsub, int n, double dvol) {
+  constexpr int U = 16;  // loads in flight
+  KSum a{0.0, 0.0}, b{0.0, 0.0};
+  for (int s = 0; s < nsub; s += U) {
+    double v[U], e[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int64_t at = (int64_t)min(s + u, nsub - 1) * n + i;
+      if (pairs) {
+        const double2 x = reinterpret_cast<const double2*>(part)[at];
+        v[u] = x.x;
+        e[u] = x.y;
+      } else {
+        v[u] = part[at];
+        e[u] = 0.0;
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; u += 2) {
+      if (s + u < nsub) {
+        kadd(a, v[u]);
+        a.c += e[u];
+      }
+      if (s + u + 1 < nsub) {
+        kadd(b, v[u + 1]);
+        b.c += e[u + 1];
+      }
+    }
+  }
+  kadd(a, b.s);
+  return dvol * (a.s + (a.c + b.c));
 }
 
 // S_r[k] (see above) of the nin inputs x(j), r = 0..R-1; tw[q] = exp(-2 pi i
@@ -132,7 +157,8 @@ __device__ __forceinline__ void transforms(X&& x, int lines, int nin, int m, int
 // (part[(c nsub + q) n1 + i], added in tile order, compensated), which
 // leaves rho as well.
 __global__ void __launch_bounds__(256) field_forward_kernel(FieldPlan p, const double* __restrict__ part,
-                                                            int nsub, double dvol,
+                                                            bool pairs, int nsub,
+                                                            double dvol,
                                                             double* __restrict__ rho,
                                                             double2* __restrict__ out,
                                                             const double2* __restrict__ tw) {
@@ -145,22 +171,8 @@ __global__ void __launch_bounds__(256) field_forward_kernel(FieldPlan p, const d
   if (part) {
     for (int t = threadIdx.x; t < cols * n1; t += blockDim.x) {
       const int c = t / n1, i = t - c * n1;
-      const double* q = part + ((int64_t)(c0 + c) * nsub) * n1 + i;
-      KSum a{0.0, 0.0}, b{0.0, 0.0};
-      int s = 0;
-      for (; s + 8 <= nsub; s += 8) {
-        double v[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = q[(int64_t)(s + u) * n1];
-#pragma unroll
-        for (int u = 0; u < 8; u += 2) {
-          kadd(a, v[u]);
-          kadd(b, v[u + 1]);
-        }
-      }
-      for (; s < nsub; ++s) kadd(a, q[(int64_t)s * n1]);
-      kadd(a, b.s);
-      const double r = dvol * (a.s + (a.c + b.c));
+      const int64_t at = ((int64_t)(c0 + c) * nsub) * n1 + i;
+      const double r = sum_rows(part, pairs, at, nsub, n1, dvol);
       x[c * pitch + i] = r;
       rho[(int64_t)i * C + c0 + c] = r;
     }
@@ -374,13 +386,13 @@ hipError_t allow_lds(const void* k, size_t lds) {
 }
 }  // namespace
 
-hipError_t launch_field_forward(const FieldPlan& p, const double* part, int nsub, double dvol,
-                                double* rho, double2* bufA, const double2* tw, hipStream_t s) {
+hipError_t launch_field_forward(const FieldPlan& p, const double* part, bool pairs, int nsub,
+                                double dvol, double* rho, double2* bufA, const double2* tw, hipStream_t s) {
   hipError_t e = allow_lds(reinterpret_cast<const void*>(field_forward_kernel), p.lds1);
   if (e != hipSuccess) return e;
   const int C1 = p.n[1] * p.n[2];
   hipLaunchKernelGGL(field_forward_kernel, dim3((C1 + p.cols1 - 1) / p.cols1), dim3(256), p.lds1, s, p,
-                     part, nsub, dvol, rho, bufA, tw);
+                     part, pairs, nsub, dvol, rho, bufA, tw);
   return hipGetLastError();
 }
 
@@ -434,8 +446,8 @@ __device__ __forceinline__ void merge_lanes(KSum& v) {
 // and two launches for tables, now 6.8 us.
 template <typename T, int ORDER>
 __global__ void __launch_bounds__(kConvThreads) field_conv_kernel(
-    int n, const double* __restrict__ part, int nsub, double dvol, double* __restrict__ rho,
-    double* __restrict__ phi, double* __restrict__ accel, const double* __restrict__ conv,
+    int n, const double* __restrict__ part, bool pairs, int nsub, double dvol,
+    double* __restrict__ rho, double* __restrict__ phi, double* __restrict__ accel, const double* __restrict__ conv,
     FieldTables tabs) {
   __shared__ double x[kConvMax], kp[kConvMax], ka[kConvMax];
   const int tid = threadIdx.x;
@@ -444,22 +456,7 @@ __global__ void __launch_bounds__(kConvThreads) field_conv_kernel(
     ka[i] = conv[n + i];
     double r;
     if (part) {
-      KSum a{0.0, 0.0}, b{0.0, 0.0};
-      const double* q = part + i;
-      int s = 0;
-      for (; s + 8 <= nsub; s += 8) {
-        double v[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = q[(int64_t)(s + u) * n];
-#pragma unroll
-        for (int u = 0; u < 8; u += 2) {
-          kadd(a, v[u]);
-          kadd(b, v[u + 1]);
-        }
-      }
-      for (; s < nsub; ++s) kadd(a, q[(int64_t)s * n]);
-      kadd(a, b.s);
-      r = dvol * (a.s + (a.c + b.c));
+      r = sum_rows(part, pairs, i, nsub, n, dvol);
       if (blockIdx.x == 0) rho[i] = r;
     } else {
       r = rho[i];
@@ -553,12 +550,12 @@ hipError_t launch_conv_setup(int n, double h, int order, const double* green, co
   return hipGetLastError();
 }
 
-hipError_t launch_field_conv(int n, const double* part, int nsub, double dvol, double* rho, double* phi,
-                             double* accel, const double* conv, int dtype, int order,
+hipError_t launch_field_conv(int n, const double* part, bool pairs, int nsub, double dvol, double* rho,
+                             double* phi, double* accel, const double* conv, int dtype, int order,
                              const FieldTables& tabs, hipStream_t s) {
   constexpr int per = kConvThreads / kConvLanes;
   auto go = [&](auto kern) {
-    hipLaunchKernelGGL(kern, dim3((n + per - 1) / per), dim3(kConvThreads), 0, s, n, part, nsub, dvol, rho,
+    hipLaunchKernelGGL(kern, dim3((n + per - 1) / per), dim3(kConvThreads), 0, s, n, part, pairs, nsub, dvol, rho,
                        phi, accel, conv, tabs);
     return hipGetLastError();
   };

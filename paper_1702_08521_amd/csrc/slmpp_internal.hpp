@@ -40,6 +40,7 @@ struct SweepArgs {
                         //    number, update with nu = c dt / h, no shift)
   double* mom;          // non-null: per-tile sums of the result over each tile row
                         // (strided tiles within one velocity block), mom[tile * n + i]
+                        // (line_sweep_kernel: pairs, the sum and its error)
   // several runs of one geometry in one fast launch (batched ensembles):
   // tile t belongs to run t / tpr, whose f and pencil table are fmulti[r]
   // and tmulti[r] (null: the single run f, table)
@@ -276,10 +277,10 @@ struct FieldTables {
   double dt;
 };
 FieldPlan plan_field(int D, const int64_t* nx, const double* h, int order, bool isolated);
-// Density (rho, or from row sums `part`: see field_forward_kernel) and its
-// transform along x_1 into bufA; then the rest, phi and accel.
-hipError_t launch_field_forward(const FieldPlan& p, const double* part, int nsub, double dvol,
-                                double* rho, double2* bufA, const double2* tw, hipStream_t s);
+// Density (rho, or from row sums `part`, pairs or not: see field_forward_kernel)
+// and its transform along x_1 into bufA; then the rest, phi and accel.
+hipError_t launch_field_forward(const FieldPlan& p, const double* part, bool pairs, int nsub,
+                                double dvol, double* rho, double2* bufA, const double2* tw, hipStream_t s);
 hipError_t launch_field_rest(const FieldPlan& p, double* phi, double* accel, double2* bufA,
                              double2* bufB, double* phi_ext, const double2* tw, const double* green,
                              int dtype, int order, const FieldTables& tabs, hipStream_t s);
@@ -288,17 +289,17 @@ hipError_t launch_field_rest(const FieldPlan& p, double* phi, double* accel, dou
 constexpr int kConvMax = 1024;
 hipError_t launch_conv_setup(int n, double h, int order, const double* green, const double2* tw,
                              double* conv, hipStream_t s);
-hipError_t launch_field_conv(int n, const double* part, int nsub, double dvol, double* rho, double* phi,
-                             double* accel, const double* conv, int dtype, int order,
+hipError_t launch_field_conv(int n, const double* part, bool pairs, int nsub, double dvol,
+                             double* rho, double* phi, double* accel, const double* conv, int dtype, int order,
                              const FieldTables& tabs, hipStream_t s);
 
 // ---- field kernels (field.hip) ----
 hipError_t launch_moment(int dtype, const void* f, int64_t nxs, int64_t nvs, double dvol,
                          double* rho, hipStream_t s);
-// rho[i * ncol + c] = dvol * sum_{q < nsub} part[(c * nsub + q) * n + i]: the
-// velocity moment from the row sums of a fused x_1 sweep (ncol spatial
-// columns of x_2..x_D, nsub tiles per velocity block).
-hipError_t launch_moment_reduce(const double* part, int n, int64_t ncol, int64_t nsub, double dvol,
+// rho[i * ncol + c] = dvol * sum_{q < nsub} part[(c * nsub + q) * n + i] (pairs:
+// sums with their errors): the velocity moment from the row sums of a fused x_1
+// sweep (ncol spatial columns of x_2..x_D, nsub tiles per velocity block).
+hipError_t launch_moment_reduce(const double* part, bool pairs, int n, int64_t ncol, int64_t nsub, double dvol,
                                 double* rho, hipStream_t s);
 hipError_t launch_poisson(const double* rho, double* phi, double* accel, double2* bufA,
                           double2* bufB, const double2* twiddles, const int64_t* tw_off,

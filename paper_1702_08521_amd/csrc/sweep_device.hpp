@@ -310,6 +310,40 @@ __device__ __forceinline__ void store_ct(T* col, int n, int m0, const T* out) {
   for (int k = 0; k < RC; ++k) op[k * DIR * STRIDE] = out[k];
 }
 
+// Compensated sums: s + c, each addition exact in s plus its rounding error in
+// c (Knuth's two-sum, no comparison of the magnitudes).
+struct KSum {
+  double s, c;
+};
+__device__ __forceinline__ void kadd(KSum& a, double x) {
+  const double t = a.s + x;
+  const double b = t - a.s;
+  a.c += (a.s - (t - b)) + (x - b);
+  a.s = t;
+}
+__device__ __forceinline__ void kmerge(KSum& a, const KSum& b) {
+  kadd(a, b.s);
+  a.c += b.c;
+}
+
+// Adds to a pair that of another lane, which must be active, by a data-parallel
+// permute: a few cycles where a shuffle goes through the LDS.  The row of 16
+// lanes mirrored, its halves mirrored, its quads reversed and its pairs swapped,
+// one after the other (the last m of them), sum over 16 lanes (over 2^m).
+constexpr int kRowMirror = 0x140, kHalfMirror = 0x141, kQuadReverse = 0x1b, kPairSwap = 0xb1;
+template <int CTRL>
+__device__ __forceinline__ double dpp_move(double v) {
+  const int64_t b = __double_as_longlong(v);
+  const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, 0xf, 0xf, true);
+  const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), CTRL, 0xf, 0xf, true);
+  return __longlong_as_double((int64_t)(((uint64_t)hi << 32) | lo));
+}
+template <int CTRL>
+__device__ __forceinline__ void merge_dpp(KSum& v) {
+  const KSum o{dpp_move<CTRL>(v.s), dpp_move<CTRL>(v.c)};
+  kmerge(v, o);
+}
+
 // 16-byte vectors as native clang vector types (kept in registers)
 typedef float vf4 __attribute__((ext_vector_type(4)));
 typedef double vd2 __attribute__((ext_vector_type(2)));

@@ -5,6 +5,7 @@
 
 #include <algorithm>
 #include <cstdint>
+#include <type_traits>
 
 #include "slmpp_internal.hpp"
 #include "sweep_device.hpp"
@@ -373,26 +374,44 @@ line_sweep_kernel(SweepArgs a, LinePlan pl, const PencilEntry<T>* __restrict__ t
     }
     if constexpr (!BLK && MODE != LINE_RK) {
       if (a.mom != nullptr) {
-        // row sums for the velocity moment: 16 lanes per tile row, each its
-        // vectors of the row in double, combined in a fixed order
-        const int q = tid & 15;
-        for (int i = tid >> 4; i < n; i += blockDim.x >> 4) {
-          const T* row = tile + (i + G) * rs;
-          double v = 0.0;
-          for (int c = q * VN; c < w.valid; c += 16 * VN) {
-            const V x = *reinterpret_cast<const V*>(row + c);
-            if (c + VN <= w.valid) {
-              v += vsum(x);
-            } else {
+        // row sums for the velocity moment: L lanes per tile row, as few as give
+        // every thread a row (fewer lanes add more and combine less), each its
+        // vectors of the row in double, compensated, combined in a fixed order
+        auto row_sums = [&](auto lanes) {
+          constexpr int L = decltype(lanes)::value;
+          const int q = tid % L;
+          for (int i = tid / L; i < n; i += blockDim.x / L) {
+            const T* row = tile + (i + G) * rs;
+            KSum v{0.0, 0.0};
+            auto add = [&](int c0, int c1) {
+              for (int c = c0; c < c1; c += L * VN) {
+                const V x = *reinterpret_cast<const V*>(row + c);
+                if (c + VN <= w.valid) {
+                  kadd(v, vsum(x));
+                } else {
 #pragma unroll
-              for (int m = 0; m < VN; ++m)
-                if (c + m < w.valid) v += (double)x[m];
-            }
+                  for (int m = 0; m < VN; ++m)
+                    if (c + m < w.valid) kadd(v, (double)x[m]);
+                }
+              }
+            };
+            // neighbouring rows begin at different vectors, on different banks
+            const int first = L < 16 && w.valid > 4 * L * VN ? (i & 3) * L * VN : 0;
+            add(first + q * VN, w.valid);
+            if (L < 16) add(q * VN, first);
+            if (L > 8) merge_dpp<kRowMirror>(v);
+            if (L > 4) merge_dpp<kHalfMirror>(v);
+            merge_dpp<kQuadReverse>(v);
+            merge_dpp<kPairSwap>(v);
+            if (q == 0) *reinterpret_cast<double2*>(a.mom + 2 * (t * n + i)) = make_double2(v.s, v.c);
           }
-#pragma unroll
-          for (int off = 1; off < 16; off <<= 1) v += __shfl_xor(v, off, 16);
-          if (q == 0) a.mom[t * n + i] = v;
-        }
+        };
+        if (4 * n >= (int)blockDim.x)
+          row_sums(std::integral_constant<int, 4>{});
+        else if (8 * n >= (int)blockDim.x)
+          row_sums(std::integral_constant<int, 8>{});
+        else
+          row_sums(std::integral_constant<int, 16>{});
         __syncthreads();
       }
     }

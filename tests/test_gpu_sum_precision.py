@@ -6,7 +6,8 @@ the two cells costs at most the seven ones beside it; everything else is exact
 (cells of unit volume): densities to 14, a mean velocity along an axis on which
 the two cells agree to 14 times the largest velocity over the number of cells
 for the numerator and as much for the denominator.  The diagnostics compensate
-every value and are exact."""
+every value and are exact.  Row sums of an x sweep add vectors of at most four
+cells plainly: the density to 6."""
 import numpy as np
 import pytest
 
@@ -82,4 +83,27 @@ def test_diagnostics(S, storage):
     flat[41234] = -BIG
     print(f"case diagnostics storage={storage}", flush=True)
     assert ctx.diag()["mass"] == flat.numel() - 2
+    ctx.close()
+
+
+@pytest.mark.parametrize("storage", [0, 1])
+@pytest.mark.parametrize("nx,nv", [([64], [128]), ([50], [611]), ([40, 50], [50, 53])])
+def test_row_sums_of_the_x_sweep(S, nx, nv, storage):
+    """A step of no duration keeps f; its density comes from the row sums."""
+    import torch
+
+    D = len(nx)
+    ctx = S.Context(S.make_desc(_spec(nx, nv, kappa=0.0), storage))
+    f = ctx.f.view(-1, int(np.prod(nv)))
+    f.fill_(1.0)
+    f[:, 11] = BIG
+    f[:, 75] = -BIG
+    before = ctx.f.clone()
+    ctx.timing_enable(True)
+    ctx.step(0.0, 1)
+    assert ctx.timing_read()["sweep_x1_moment"]["launches"] == 1
+    assert torch.equal(ctx.f, before)
+    rho, _ = ctx.get_field()
+    print(f"case row sums nx={nx} nv={nv} storage={storage}", flush=True)
+    assert np.abs(rho - (np.prod(nv) - 2)).max() <= 6
     ctx.close()
