@@ -223,6 +223,14 @@ slmpp_status slmpp_advect_v(slmpp_ctx* ctx, int32_t dim, double dt, const double
 slmpp_status slmpp_advect_v_noalloc(const slmpp_grid_desc* desc, void* f_dev, int32_t dim,
                                     double dt, const double* accel_dev, void* hip_stream);
 
+/* The kernel that a sweep along array axis `axis` runs in when it is made by
+ * itself (slmpp_advect_x: 0..D-1, by dt; slmpp_advect_v: D..2D-1, any dt):
+ * 3: persistent tiles with run-time sizes, 2: persistent tiles with
+ * compile-time sizes, 1: one tile per workgroup with compile-time segments,
+ * 0: the same with run-time ones; -1: invalid arguments, or the pencils do
+ * not fit.  Looks at the sizes only: no device is needed. */
+int32_t slmpp_sweep_route(const slmpp_grid_desc* desc, int32_t axis, double dt);
+
 /* One velocity kick: SL steps along v_1, .., v_D in that order, each by dt
  * with the context's acceleration (computed from f first when f changed
  * since the last field solve), as in the half-kicks of slmpp_step: the last

@@ -19,6 +19,7 @@ using namespace slmpp;
 namespace {
 
 constexpr int64_t kMaxAxis = 4096;               // LDS holds a whole pencil
+constexpr size_t kMaxLds = 160 * 1024;           // of a workgroup
 constexpr int64_t kMaxCells = (int64_t)1 << 40;  // 1.1e12 cells
 // row sums that every workgroup of the one-dimensional field solve adds up;
 // more are left to the moment over f (1024 cells by 256 tiles: 256 KB for
@@ -218,6 +219,31 @@ SweepArgs v_sweep_args(const slmpp_grid_desc& d, const int64_t* dims, int l, dou
 bool line_preferred(const SweepPlan& p, const SweepArgs& a) {
   return !p.fast || a.rk || a.npen * a.n < kSmallCells || (a.inner > 1 && (p.W == 32 || (p.W == 48 && a.inner > 256)));
 }
+
+// The plans of a sweep; line.lds_bytes != 0: line_sweep_kernel.  sums > 0: its
+// tiles may leave the row sums of the velocity moment, within velocity blocks
+// of that many cells and up to max_sums of them (*with_sums: whether they do).
+struct SweepRoute {
+  SweepPlan tile;
+  LinePlan line;
+};
+SweepRoute route_sweep(const slmpp_grid_desc& d, const SweepArgs& s, int64_t sums = 0, int64_t max_sums = 0,
+                       bool moment = false, bool* with_sums = nullptr) {
+  SweepRoute r{};
+  r.tile = plan_sweep(d.storage, d.order, d.limiter, s.n, s.npen, s.inner, s.nfast, 0, 0, moment);
+  if (r.tile.lds_bytes > kMaxLds) return r;
+  if (sums > 0) {
+    r.line = plan_line(d.storage, d.order, s, sums);
+    if (r.line.lds_bytes && r.line.tiles * (int64_t)s.n <= max_sums &&
+        line_preferred(r.tile, s)) {
+      *with_sums = true;
+      return r;
+    }
+  }
+  r.line = plan_line(d.storage, d.order, s, 0);
+  if (r.line.lds_bytes && !line_preferred(r.tile, s)) r.line = LinePlan{};
+  return r;
+}
 }  // namespace
 
 struct slmpp_ctx {
@@ -270,6 +296,21 @@ struct slmpp_ctx {
   int64_t mom_sub = 1;  // tiles per velocity block of the last fused x_1 sweep
   bool mom_pairs = false;  // whether it left pairs
   size_t esize() const { return d.storage == SLMPP_F64 ? 8 : 4; }
+
+  void set_grid(const slmpp_grid_desc& desc) {
+    d = desc;
+    D = d.D;
+    rk = (d.flags & SLMPP_FLAG_RK3) != 0;
+    for (int l = 0; l < D; ++l) {
+      dims[l] = d.nx[l];
+      dims[D + l] = d.nv[l];
+      hx[l] = (d.x_hi[l] - d.x_lo[l]) / (double)d.nx[l];
+      hv[l] = (d.v_hi[l] - d.v_lo[l]) / (double)d.nv[l];
+    }
+    nxs = n_space(d);
+    nvs = n_vel(d);
+    ncell = nxs * nvs;
+  }
 
   slmpp_status fail(slmpp_status code, const char* fmt, ...) {
     char buf[512];
@@ -405,29 +446,23 @@ struct slmpp_ctx {
     if (fused) *fused = false;
     if (done) *done = 1;
     const int64_t inner = s.inner;
-    SweepPlan p = plan_sweep(d.storage, d.order, d.limiter, s.n, s.npen, inner, s.nfast, 0, 0,
-                             fuse_moment && !rk && a == 0);
-    if (p.lds_bytes > 160 * 1024)
+    // (row sums save a pass over f; in one dimension, where the solve adds
+    // them up itself, a launch)
+    const bool moment = fuse_moment && !rk && a == 0;
+    bool sums = false;
+    const SweepRoute route = route_sweep(d, s, moment && (D == 1 ? conv_field : nvs >= 64) ? nvs : 0,
+                                         lay.mom_doubles, moment, &sums);
+    const SweepPlan& p = route.tile;
+    LinePlan lp = route.line;
+    if (p.lds_bytes > kMaxLds)
       return fail(SLMPP_ERR_SHAPE, "pencil of %d cells does not fit the LDS tile", s.n);
-    LinePlan lp{};
-    if (line_preferred(p, s)) {
-      // (row sums save a pass over f; in one dimension, where the solve adds
-      // them up itself, a launch)
-      if (fuse_moment && !rk && a == 0 &&
-          (D == 1 ? conv_field : nvs >= 64)) {
-        lp = plan_line(d.storage, d.order, s, nvs);
-        if (lp.lds_bytes && lp.tiles * (int64_t)s.n <= lay.mom_doubles) {
-          s.mom = mom();
-          mom_sub = lp.tpb;
-          mom_pairs = true;
-          if (fused) *fused = true;
-        } else {
-          lp = LinePlan{};
-        }
-      }
-      if (!lp.lds_bytes) lp = plan_line(d.storage, d.order, s, 0);
+    if (sums) {
+      s.mom = mom();
+      mom_sub = lp.tpb;
+      mom_pairs = true;
+      if (fused) *fused = true;
     }
-    if (!lp.lds_bytes && fuse_moment && !rk && a == 0 && p.fast && p.W >= 64 && inner > 1 &&
+    if (!lp.lds_bytes && moment && p.fast && p.W >= 64 && inner > 1 &&
         nvs % p.W == 0 && p.tiles * (int64_t)s.n <= lay.mom_doubles) {
       s.mom = mom();
       mom_sub = nvs / p.W;
@@ -805,23 +840,12 @@ slmpp_status slmpp_create(const slmpp_grid_desc* desc, void* f_dev, void* work_d
       return SLMPP_ERR_WORKSPACE;
     }
     slmpp_ctx* c = new slmpp_ctx();
-    c->d = *desc;
+    c->set_grid(*desc);
     c->f = f_dev;
     c->work = static_cast<char*>(work_dev);
     c->work_bytes = work_bytes;
     c->stream = static_cast<hipStream_t>(hip_stream);
     c->lay = lay;
-    c->D = desc->D;
-    c->rk = (desc->flags & SLMPP_FLAG_RK3) != 0;
-    for (int l = 0; l < c->D; ++l) {
-      c->dims[l] = desc->nx[l];
-      c->dims[c->D + l] = desc->nv[l];
-      c->hx[l] = (desc->x_hi[l] - desc->x_lo[l]) / (double)desc->nx[l];
-      c->hv[l] = (desc->v_hi[l] - desc->v_lo[l]) / (double)desc->nv[l];
-    }
-    c->nxs = n_space(*desc);
-    c->nvs = n_vel(*desc);
-    c->ncell = c->nxs * c->nvs;
     // Green function table and twiddles
     std::vector<double> green(c->nxs);
     for (int64_t idx = 0; idx < c->nxs; ++idx) {
@@ -1008,9 +1032,10 @@ slmpp_status slmpp_advect_v_noalloc(const slmpp_grid_desc* desc, void* f_dev, in
   if (dt == 0.0) return SLMPP_OK;
   int64_t inner = 1;
   const SweepArgs s = v_sweep_args(*desc, dims, dim, dt, accel_dev, f_dev, inner);
-  const SweepPlan p = plan_sweep(desc->storage, desc->order, desc->limiter, s.n, s.npen, inner,
-                                 s.nfast);
-  if (p.lds_bytes > 160 * 1024) {
+  const SweepRoute route = route_sweep(*desc, s);
+  const SweepPlan& p = route.tile;
+  const LinePlan& lp = route.line;
+  if (p.lds_bytes > kMaxLds) {
     g_error = "pencil of " + std::to_string(s.n) + " cells does not fit the LDS tile";
     return SLMPP_ERR_SHAPE;
   }
@@ -1020,7 +1045,6 @@ slmpp_status slmpp_advect_v_noalloc(const slmpp_grid_desc* desc, void* f_dev, in
   TableJobs jobs{};
   jobs.add(s, table, nxs);
   if (e == hipSuccess) e = launch_tables(desc->storage, desc->order, jobs, stream);
-  const LinePlan lp = line_preferred(p, s) ? plan_line(desc->storage, desc->order, s, 0) : LinePlan{};
   if (e == hipSuccess)
     e = lp.lds_bytes ? launch_line_sweep(desc->storage, desc->order, desc->limiter, s, lp, table, stream)
                      : launch_sweep(desc->storage, desc->order, desc->limiter, s, p, table, stream);
@@ -1029,6 +1053,16 @@ slmpp_status slmpp_advect_v_noalloc(const slmpp_grid_desc* desc, void* f_dev, in
     return SLMPP_ERR_DEVICE;
   }
   return SLMPP_OK;
+}
+
+int32_t slmpp_sweep_route(const slmpp_grid_desc* desc, int32_t axis, double dt) {
+  std::string msg;
+  if (check_desc(desc, msg) != SLMPP_OK || axis < 0 || axis >= 2 * desc->D || !std::isfinite(dt)) return -1;
+  slmpp_ctx c;
+  c.set_grid(*desc);
+  const SweepRoute r = route_sweep(*desc, c.sweep_args(axis, dt, nullptr));
+  if (r.tile.lds_bytes > kMaxLds) return -1;
+  return r.line.lds_bytes ? 3 : (r.tile.fast ? 2 : (r.tile.R > 0 ? 1 : 0));
 }
 
 slmpp_status slmpp_kick(slmpp_ctx* c, double dt) {

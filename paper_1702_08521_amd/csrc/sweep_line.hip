@@ -489,7 +489,10 @@ LinePlan plan_line(int dtype, int order, const SweepArgs& a, int64_t moment_bloc
   };
   int threads = a.rk ? kLineThreadsSmall : kLineThreads;
   if (!tile_of(threads)) return p;
-  const bool blk = moment_block <= 0 && inner <= std::max(pwmax, 48);
+  // block tiles: whole blocks of few pencils; row tiles where one block needs
+  // more threads than there are or overflows the LDS
+  const bool blk = moment_block <= 0 && inner <= std::max(pwmax, 48) && inner * S <= threads &&
+                   inner * percell + 32 * es <= (int64_t)kLineLdsMax;
   if (blk && es == 8 && !a.rk) {
     const LinePlan wide = p;
     const int S0 = S, pw0 = pwmax;

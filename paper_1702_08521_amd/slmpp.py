@@ -96,6 +96,7 @@ SIGNATURES = {
     "slmpp_advect_x": (_S, [_VP, _I32, _D]),
     "slmpp_advect_v": (_S, [_VP, _I32, _D, _VP]),
     "slmpp_advect_v_noalloc": (_S, [_VP, _VP, _I32, _D, _VP, _VP]),
+    "slmpp_sweep_route": (_I32, [ctypes.POINTER(GridDesc), _I32, _D]),
     "slmpp_kick": (_S, [_VP, ctypes.c_double]),
     "slmpp_density_moment": (_S, [_VP, _VP]),
     "slmpp_poisson_solve": (_S, [_VP, _VP, _VP, _VP]),
@@ -191,6 +192,11 @@ def make_desc(spec, storage=F64) -> GridDesc:
 
 def workspace_bytes(desc: GridDesc) -> int:
     return int(lib().slmpp_workspace_bytes(ctypes.byref(desc)))
+
+
+def sweep_route(desc: GridDesc, axis, dt=0.0) -> int:
+    """The kernel a single sweep along `axis` runs in (slmpp_sweep_route)."""
+    return int(lib().slmpp_sweep_route(ctypes.byref(desc), int(axis), float(dt)))
 
 
 def validate(desc: GridDesc):
