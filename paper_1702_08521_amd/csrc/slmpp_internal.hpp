@@ -148,6 +148,7 @@ struct LinePlan {
   int64_t bstride;     // elements between blocks of row tiles
   int64_t tiles;
   int32_t reps;        // block tiles: sweeps of the tile one after the other
+  int32_t stream;      // row tiles: nontemporal accesses
   FastDiv32 dtpb, dvdiv, dnvl, dxdiv;
   size_t lds_bytes;    // 0: the sweep is not one this kernel takes
 };

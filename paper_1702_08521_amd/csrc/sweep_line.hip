@@ -23,6 +23,11 @@ constexpr int kLineMaxR = sizeof(T) == 4 ? 16 : 8;
 constexpr int kLineThreads = 512, kLineThreadsSmall = 256;
 constexpr size_t kLineLds = 40 * 1024;     // preferred LDS of a tile: four workgroups per CU
 constexpr size_t kLineLdsMax = 80 * 1024;  // at most (long pencils)
+// a workgroup of five wavefronts leaves the four SIMDs of a CU unevenly filled:
+// its sweeps took as long as those of one-tile workgroups or longer, where four,
+// seven or eight wavefronts took 0.6-0.8 of them (n 96, s 44, 1.3e8 cells FP64: 820 us,
+// with two tiles of three wavefronts each 553)
+constexpr int kUneven = 5;
 
 // MODE of line_sweep_kernel: one sweep; all three TVD-RK stages; pl.reps
 // sweeps of block tiles one after the other (the same kick twice, with one
@@ -56,7 +61,7 @@ enum : int { LINE_ONE = 0, LINE_RK = 1, LINE_REPEAT = 2 };
 // 11.9 ms for that step), steps between a thread's vectors kept in scalar
 // registers, and loads without a second path for partial vectors (whose
 // merge made every load wait for the one before: 7.34 ms).
-template <typename T, int ORDER, int LIM, bool BLK, int MODE>
+template <typename T, int ORDER, int LIM, bool BLK, int MODE, bool STREAM>
 __global__ void __attribute__((amdgpu_flat_work_group_size(1, MODE == LINE_RK ? kLineThreadsSmall : kLineThreads),
                                amdgpu_waves_per_eu(MODE == LINE_RK ? 3 : (MODE == LINE_REPEAT ? 2 : 4))))
 line_sweep_kernel(SweepArgs a, LinePlan pl, const PencilEntry<T>* __restrict__ table) {
@@ -167,8 +172,10 @@ line_sweep_kernel(SweepArgs a, LinePlan pl, const PencilEntry<T>* __restrict__ t
     const T* src = f + w.base;
 #pragma unroll
     for (int k = 0; k < NS; ++k)
-      if (k < nslot && exist(w, k) > 0)
-        pf[k] = __builtin_nontemporal_load((GlobalPtr<const U>)(src + k * gstep + goff0));
+      if (k < nslot && exist(w, k) > 0) {
+        const GlobalPtr<const U> q = (GlobalPtr<const U>)(src + k * gstep + goff0);
+        pf[k] = STREAM ? __builtin_nontemporal_load(q) : *q;
+      }
   };
   // LDS element of component c of vector k
   auto at = [&](int k, int c) -> int {
@@ -363,7 +370,10 @@ line_sweep_kernel(SweepArgs a, LinePlan pl, const PencilEntry<T>* __restrict__ t
           }
           T* p = dst + k * gstep + goff0;
           if (whole || c1 >= VN) {
-            __builtin_nontemporal_store((U)v, (GlobalPtr<U>)p);
+            if constexpr (STREAM)
+              __builtin_nontemporal_store((U)v, (GlobalPtr<U>)p);
+            else
+              *(GlobalPtr<U>)p = (U)v;
           } else {
 #pragma unroll
             for (int c = 0; c < VN; ++c)
@@ -420,9 +430,9 @@ line_sweep_kernel(SweepArgs a, LinePlan pl, const PencilEntry<T>* __restrict__ t
   }
 }
 
-template <typename T, int ORDER, int LIM, bool BLK, int MODE>
+template <typename T, int ORDER, int LIM, bool BLK, int MODE, bool STREAM = true>
 hipError_t launch_t(const SweepArgs& a, const LinePlan& p, const void* table, hipStream_t s) {
-  auto kern = line_sweep_kernel<T, ORDER, LIM, BLK, MODE>;
+  auto kern = line_sweep_kernel<T, ORDER, LIM, BLK, MODE, STREAM>;
   const void* fn = reinterpret_cast<const void*>(kern);
   hipError_t e = hipSuccess;
   if (p.lds_bytes > 64 * 1024)
@@ -440,12 +450,15 @@ hipError_t launch_t(const SweepArgs& a, const LinePlan& p, const void* table, hi
 
 template <typename T, int ORDER, int LIM>
 hipError_t launch_l(const SweepArgs& a, const LinePlan& p, const void* table, hipStream_t s) {
-  if (a.rk)
-    return p.K ? launch_t<T, ORDER, LIM, true, LINE_RK>(a, p, table, s)
-               : launch_t<T, ORDER, LIM, false, LINE_RK>(a, p, table, s);
+  if (a.rk) {
+    if (p.K) return launch_t<T, ORDER, LIM, true, LINE_RK>(a, p, table, s);
+    return p.stream ? launch_t<T, ORDER, LIM, false, LINE_RK>(a, p, table, s)
+                    : launch_t<T, ORDER, LIM, false, LINE_RK, false>(a, p, table, s);
+  }
   if (p.K && p.reps > 1) return launch_t<T, ORDER, LIM, true, LINE_REPEAT>(a, p, table, s);
-  return p.K ? launch_t<T, ORDER, LIM, true, LINE_ONE>(a, p, table, s)
-             : launch_t<T, ORDER, LIM, false, LINE_ONE>(a, p, table, s);
+  if (p.K) return launch_t<T, ORDER, LIM, true, LINE_ONE>(a, p, table, s);
+  return p.stream ? launch_t<T, ORDER, LIM, false, LINE_ONE>(a, p, table, s)
+                  : launch_t<T, ORDER, LIM, false, LINE_ONE, false>(a, p, table, s);
 }
 
 template <typename T, int ORDER>
@@ -477,8 +490,8 @@ LinePlan plan_line(int dtype, int order, const SweepArgs& a, int64_t moment_bloc
                  : (cells >= ((int64_t)1 << 19) || moment_block > 0 ? 8 : 4);
   const int64_t percell = (n + 2 * p.G) * es;  // LDS bytes per pencil
   int S = 0, pwmax = 0;
-  auto tile_of = [&](int threads) {
-    S = (int)((n + Rt - 1) / Rt);
+  auto tile_of = [&](int threads, int rt) {
+    S = (int)((n + rt - 1) / rt);
     if (S > threads / vn) S = (int)((n + maxr - 1) / maxr);
     if (S > threads / vn) return false;
     p.R = (int)((n + S - 1) / S);
@@ -487,16 +500,20 @@ LinePlan plan_line(int dtype, int order, const SweepArgs& a, int64_t moment_bloc
     pwmax = std::min<int>(threads / S, (int)std::max<int64_t>(kLineLds / percell, 1));
     return true;
   };
+  auto waves = [&](int64_t pencils) { return (int)((pencils * S + 63) / 64); };
   int threads = a.rk ? kLineThreadsSmall : kLineThreads;
-  if (!tile_of(threads)) return p;
+  if (!tile_of(threads, Rt)) return p;
   // block tiles: whole blocks of few pencils; row tiles where one block needs
-  // more threads than there are or overflows the LDS
+  // more threads than there are, overflows the LDS, or is of many pencils and
+  // fills five wavefronts
   const bool blk = moment_block <= 0 && inner <= std::max(pwmax, 48) && inner * S <= threads &&
-                   inner * percell + 32 * es <= (int64_t)kLineLdsMax;
+                   inner * percell + 32 * es <= (int64_t)kLineLdsMax && !(inner > 48 && waves(inner) == kUneven);
+  // row tiles narrower than 64 bytes take longer segments
+  if (!blk && pwmax * es < 64 && Rt == 8 && maxr > 8 && !tile_of(threads, maxr)) return LinePlan{};
   if (blk && es == 8 && !a.rk) {
     const LinePlan wide = p;
     const int S0 = S, pw0 = pwmax;
-    if (tile_of(kLineThreadsSmall) && pwmax >= inner) {
+    if (tile_of(kLineThreadsSmall, Rt) && pwmax >= inner) {
       threads = kLineThreadsSmall;
     } else {
       p = wide;
@@ -528,12 +545,21 @@ LinePlan plan_line(int dtype, int order, const SweepArgs& a, int64_t moment_bloc
     p.blen = (int)(moment_block > 0 ? moment_block : inner);
     p.blocks = a.npen / p.blen;
     p.bstride = moment_block > 0 ? moment_block : n * inner;
+    // rows of whole 64-byte pieces where every row starts on one
+    const int line = 64 / es;
+    const bool lines = inner % line == 0 && p.blen % line == 0;
     int w = std::max(vn, pwmax / vn * vn);
+    if (lines && w >= line) w = w / line * line;
     int64_t tpb = (p.blen + w - 1) / w;
-    auto width = [&](int64_t tb) { return (int)(((p.blen + tb - 1) / tb + vn - 1) / vn * vn); };
+    auto width = [&](int64_t tb) {
+      const int x = (int)(((p.blen + tb - 1) / tb + vn - 1) / vn * vn);
+      return lines && x > line ? (x + line - 1) / line * line : x;
+    };
     // (row sums: fewer, wider tiles, whose sums the field solve adds up)
-    const int least = moment_block > 0 ? 64 : 8;
+    const int least = moment_block > 0 ? 64 : (Rt > 4 ? line : 8);
     while (tpb * p.blocks < kWant && width(2 * tpb) >= least && width(2 * tpb) * S >= 64) tpb *= 2;
+    if (waves(width(tpb)) == kUneven)
+      while (width(tpb) > least && waves(width(tpb)) >= kUneven) ++tpb;
     p.W = width(tpb);
     p.tpb = (int)((p.blen + p.W - 1) / p.W);
     p.pw = p.W;
@@ -549,6 +575,12 @@ LinePlan plan_line(int dtype, int order, const SweepArgs& a, int64_t moment_bloc
   p.dvdiv = FastDiv32::of((uint32_t)std::max<int64_t>(1, std::min<int64_t>(a.vdiv, 0x7fffffff)));
   p.dnvl = FastDiv32::of((uint32_t)std::max(1, a.nvl));
   p.dxdiv = FastDiv32::of((uint32_t)std::max<int64_t>(1, std::min<int64_t>(a.xdiv, 0x7fffffff)));
+  // Nontemporal accesses, but for rows that share lines with the rows of the
+  // next tile, on grids beyond the L2: those lines would be fetched and written
+  // twice (n 64, s 250, 3e7 cells FP32: 80 us nontemporal, 60 through the caches;
+  // 1000-cell pencils, s 64, FP64 TVD-RK 237 / 136; 30x37 x 54x61 FP32, in L2,
+  // 84 / 86 per step).
+  p.stream = cells * es <= ((int64_t)1 << 25) || p.W * es >= 512;
   p.reps = 1;
   p.lds_bytes = lds;
   return p;

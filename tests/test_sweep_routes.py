@@ -26,6 +26,11 @@ CASES = [
     ([2, 2], [500, 46], 0, W.LIM_NONE, "sl", {2: 3}),
     ([128], [40], 0, W.LIM_MP, "sl", {0: 3}),
     ([256], [44], 1, W.LIM_MP, "sl", {0: 3}),
+    # rows that would be narrower than 64 bytes, and rows of whole 64-byte pieces
+    ([5, 5], [384, 64], 1, W.LIM_MP, "sl", {2: 3}),
+    ([9, 50], [60, 32], 1, W.LIM_MP, "sl", {1: 3, 2: 3}),
+    # blocks of more than 48 pencils that fill five wavefronts
+    ([13, 13], [40, 64], 1, W.LIM_MP, "sl", {2: 3}),
 ]
 
 
