@@ -207,17 +207,48 @@ SweepArgs v_sweep_args(const slmpp_grid_desc& d, const int64_t* dims, int l, dou
   return s;
 }
 
-// Whether a sweep goes to line_sweep_kernel (when that takes it): sizes
-// without a compile-time tile, other limiters and TVD-RK; and instead of the
-// narrow tiles of sweep_fast_kernel, 48 pencils where the stride has room for
-// wider rows (18 x 20 x 24 x 30 x 36 x 42 FP32, x3 sweep: 861 -> 715 us; at a
-// stride of 48 both take the same time) and 32 pencils (36 x 36 x 24 x 16 x
-// 16 x 32 FP64, v2 sweep: 1362 -> 889 us).  The wider tiles of
-// sweep_fast_kernel are up to 30% faster than line_sweep_kernel, except on
-// grids too small to fill the GPU with them (64 x 48 FP64 step 31.3 -> 28.4
-// us, 16^2 x 32^2 FP64 52.3 -> 50.0 us; from half a million cells on equal).
-bool line_preferred(const SweepPlan& p, const SweepArgs& a) {
-  return !p.fast || a.rk || a.npen * a.n < kSmallCells || (a.inner > 1 && (p.W == 32 || (p.W == 48 && a.inner > 256)));
+// Whether a sweep that line_sweep_kernel takes (plan lp) goes to it rather
+// than to the kernel of plan p.  Run-time lengths, other limiters and TVD-RK
+// always do.  Compile-time tiles (p.R cells per thread) against it, us per
+// sweep, first their time, then line_sweep_kernel's (n: cells of a pencil, s:
+// its stride; v, x: velocity and space sweeps):
+//  * sweep_fast_kernel is faster or equal, except on small grids (64 x 48
+//    FP64 step 31.3 / 28.4, 16^2 x 32^2 FP64 52.3 / 50.0; from 2^18 cells
+//    equal), with tiles of half a wavefront (16-cell pencils in 32s: 35 / 27
+//    at 7e6 cells FP64), and in 32s and 48s of pencils for large FP32 v sweeps
+//    (n 24, s 2160, 2^27 cells 270 / 227; at s 336, or x, up to 10% faster
+//    itself) and FP64 24-cell segments (n 72, s 720: 690 / 560);
+//  * one tile per workgroup is slower (n 64, s 250, 3e7 cells FP32 83 / 60;
+//    n 24, s 44 FP64 167 / 156), except where its tiles are wide: FP64 x
+//    sweeps (n 128, s 100, 3e7 cells 159 / 187), blocks that leave a tile of
+//    line_sweep_kernel five wavefronts (n 48, s 44, 1.3e8 cells FP64 561 / 704),
+//    large FP64 contiguous pencils (n 3072, 3e7 cells 112 / 132), and, for up
+//    to 4e6 cells, too few tiles to have one loaded ahead, FP32 x sweeps (n 48,
+//    s 100: 22.7 / 27.9) and long pencils (n 384, s 576: 15.3 / 20.0).  FP64 x
+//    sweeps in two segments over long strides keep line_sweep_kernel (n 24,
+//    s 1764, 3e7 cells 162 / 156; n 32, s 3000, 4e6 cells 31 / 27).
+// sums: with the row sums of the velocity moment, which save a pass over f
+// where the tiles of sweep_fast_kernel cannot leave them (12 x 24 x 86^2 FP64,
+// four steps: 494 / 463).
+bool line_preferred(int dtype, const SweepPlan& p, const SweepArgs& a, const LinePlan& lp, bool sums) {
+  if (a.rk || p.R == 0) return true;
+  const int64_t cells = a.npen * a.n;
+  const bool f64 = dtype == SLMPP_F64, x = a.cmode == SPEED_FROM_VELOCITY;
+  if (p.fast) {
+    if (cells <= (f64 || lp.K > 0 ? kSmallCells : kSmallCells / 2)) return true;
+    if (a.inner == 1 || p.W > 48) return false;
+    if (sums) return true;
+    if (f64) return p.W == 32 ? p.threads < 64 : p.R == 24 && a.inner > 256;
+    return !x && a.inner >= 400 && cells >= (p.W == 48 ? (int64_t)1 << 26 : (int64_t)1 << 25);
+  }
+  if (sums || cells < ((int64_t)1 << 20) || p.S == 1) return true;
+  if (a.inner == 1) return !(f64 && cells >= ((int64_t)1 << 24));
+  const bool few = cells < ((int64_t)1 << 22);
+  if (few && a.n >= 256 && p.W >= 8) return false;
+  if (p.W < 32) return true;
+  if (a.inner <= 48 && lp.threads == 5 * 64) return false;
+  if (x && f64) return p.S == 2 && a.inner >= 512;
+  return !(x && few);
 }
 
 // The plans of a sweep; line.lds_bytes != 0: line_sweep_kernel.  sums > 0: its
@@ -235,13 +266,13 @@ SweepRoute route_sweep(const slmpp_grid_desc& d, const SweepArgs& s, int64_t sum
   if (sums > 0) {
     r.line = plan_line(d.storage, d.order, s, sums);
     if (r.line.lds_bytes && r.line.tiles * (int64_t)s.n <= max_sums &&
-        line_preferred(r.tile, s)) {
+        line_preferred(d.storage, r.tile, s, r.line, true)) {
       *with_sums = true;
       return r;
     }
   }
   r.line = plan_line(d.storage, d.order, s, 0);
-  if (r.line.lds_bytes && !line_preferred(r.tile, s)) r.line = LinePlan{};
+  if (r.line.lds_bytes && !line_preferred(d.storage, r.tile, s, r.line, false)) r.line = LinePlan{};
   return r;
 }
 }  // namespace

@@ -206,8 +206,10 @@ SweepPlan plan_sweep(int dtype, int order, int limiter, int32_t n, int64_t npen,
   p.fast = R > 0 && R % vn == 0 && fits32 && W_override == 0 &&
            (contiguous ? (W == 64 && n % vn == 0) : (inner % W == 0 && inner % vn == 0 &&
                                                      (W == 256 || W == 128 || W == 64 || W == 48 || W == 32)));
-  if (!p.fast) p.R = 0;  // compile-time segments exist in the fast kernel only
-  p.lds_bytes = lds(W, p.R > 0);
+  if (R == 32 && !p.fast) {  // 32-cell segments exist in the fast kernel only
+    p.R = 0;
+    p.lds_bytes = lds(W, false);
+  }
   return p;
 }
 

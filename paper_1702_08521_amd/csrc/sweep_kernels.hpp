@@ -383,13 +383,13 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, const SweepPlan& 
   }
 }
 
-// One tile per workgroup with run-time lengths: pencils too long or too many
-// for line_sweep_kernel.
-template <typename T, int ORDER, int LIM>
+// One tile per workgroup: pencils in segments of RC cells, or (RC 0) of a
+// run-time length (see line_preferred in api.hip for the sizes).
+template <typename T, int ORDER, int LIM, int RC>
 __global__ void __launch_bounds__(256) sweep_kernel(SweepArgs a, SweepPlan pl,
                                                     const PencilEntry<T>* __restrict__ table) {
   extern __shared__ __align__(16) unsigned char smem[];
-  sweep_tile<T, ORDER, LIM, 0, 0>(a, pl, table, (int64_t)blockIdx.x, smem);
+  sweep_tile<T, ORDER, LIM, RC, 0>(a, pl, table, (int64_t)blockIdx.x, smem);
 }
 
 // Fast path: persistent workgroups over whole tiles with software prefetch.
@@ -883,9 +883,9 @@ __global__ void __launch_bounds__(128) pencil_table_kernel(TableJobs jobs) {
     reinterpret_cast<PencilEntry<T>*>(jobs.tab[y])[idx] = pencil_entry<T, ORDER>(jobs.a[y], idx);
 }
 
-template <typename T, int ORDER, int LIM>
+template <typename T, int ORDER, int LIM, int RC>
 hipError_t launch_k(const SweepArgs& a, const SweepPlan& p, const void* table, hipStream_t s) {
-  auto kern = sweep_kernel<T, ORDER, LIM>;
+  auto kern = sweep_kernel<T, ORDER, LIM, RC>;
   if (p.lds_bytes > 64 * 1024) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                        hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -924,14 +924,16 @@ hipError_t launch_fast(const SweepArgs& a, const SweepPlan& p, const void* table
   return hipGetLastError();
 }
 
-// the persistent kernel with the plan's width and segment length
+// SL-MPP sweeps in segments of RC cells: the persistent kernel with the plan's
+// width, or one tile per workgroup
 template <typename T, int ORDER, int RC>
 hipError_t launch_w(const SweepArgs& a, const SweepPlan& p, const void* table, hipStream_t s) {
   if constexpr (RC == 32) {  // strided 128-pencil tiles of 64-cell pencils only
-    if (a.inner == 1 || p.W != 128) return hipErrorInvalidValue;
+    if (!p.fast || a.inner == 1 || p.W != 128) return hipErrorInvalidValue;
     if (a.mom) return launch_fast<T, ORDER, RC, 128, false, true>(a, p, table, s);
     return launch_fast<T, ORDER, RC, 128, false>(a, p, table, s);
   } else {
+    if (!p.fast) return launch_k<T, ORDER, SLMPP_LIM_MPP, RC>(a, p, table, s);
     if (a.inner == 1) return launch_fast<T, ORDER, RC, 64, true>(a, p, table, s);
     switch (p.W) {
       case 256:
@@ -957,17 +959,17 @@ hipError_t launch_w(const SweepArgs& a, const SweepPlan& p, const void* table, h
 template <typename T, int ORDER, int LIM>
 hipError_t launch_r(const SweepArgs& a, const SweepPlan& p, const void* table, hipStream_t s) {
   if constexpr (LIM == SLMPP_LIM_MPP) {
-    if (p.fast) switch (p.R) {
+    switch (p.R) {
       case 12: return launch_w<T, ORDER, 12>(a, p, table, s);
       case 16: return launch_w<T, ORDER, 16>(a, p, table, s);
       case 24: return launch_w<T, ORDER, 24>(a, p, table, s);
       case 32:  // planned for FP32 only
         if constexpr (sizeof(T) == 4) return launch_w<T, ORDER, 32>(a, p, table, s);
         return hipErrorInvalidValue;
-      default: return hipErrorInvalidValue;
+      default: break;
     }
   }
-  return launch_k<T, ORDER, LIM>(a, p, table, s);
+  return launch_k<T, ORDER, LIM, 0>(a, p, table, s);
 }
 
 template <typename T, int ORDER>

@@ -29,8 +29,42 @@ CASES = [
     # rows that would be narrower than 64 bytes, and rows of whole 64-byte pieces
     ([5, 5], [384, 64], 1, W.LIM_MP, "sl", {2: 3}),
     ([9, 50], [60, 32], 1, W.LIM_MP, "sl", {1: 3, 2: 3}),
+    # no tile of the run-time kernel: compile-time segments, or run-time ones
+    ([40], [1200], 0, W.LIM_MPP, "rk3", {1: 1}),
+    ([17], [3072], 0, W.LIM_MPP, "sl", {1: 1}),
+    ([5], [3001], 0, W.LIM_MPP, "sl", {1: 0}),
+    # compile-time tiles: small grids, half wavefronts, wide tiles
+    ([11, 11], [64, 64], 0, W.LIM_MPP, "sl", {2: 3, 3: 3}),
+    ([12, 11], [64, 64], 0, W.LIM_MPP, "sl", {2: 2, 3: 2}),
+    ([8, 8], [64, 64], 1, W.LIM_MPP, "sl", {2: 3, 3: 3}),
+    ([9, 9], [64, 64], 1, W.LIM_MPP, "sl", {2: 2, 3: 3}),
+    ([35, 35], [16, 32], 0, W.LIM_MPP, "sl", {2: 3}),
+    ([35, 35], [16, 32], 1, W.LIM_MPP, "sl", {2: 2}),
+    ([35, 35], [24, 32], 0, W.LIM_MPP, "sl", {2: 2}),
+    ([13, 60], [24, 30], 0, W.LIM_MPP, "sl", {1: 2}),
+    ([13, 72], [24, 30], 0, W.LIM_MPP, "sl", {1: 3}),
     # blocks of more than 48 pencils that fill five wavefronts
     ([13, 13], [40, 64], 1, W.LIM_MP, "sl", {2: 3}),
+    # one tile per workgroup: from 2^20 cells, blocks of five wavefronts, FP64 x
+    # sweeps, long pencils, FP32 x sweeps up to 2^22 cells
+    ([22, 24], [48, 44], 0, W.LIM_MPP, "sl", {2: 1}),
+    ([20, 24], [48, 44], 0, W.LIM_MPP, "sl", {2: 3}),
+    ([9, 128], [30, 31], 0, W.LIM_MPP, "sl", {1: 1}),
+    ([8, 128], [30, 31], 0, W.LIM_MPP, "sl", {1: 3}),
+    ([24, 48], [30, 31], 1, W.LIM_MPP, "sl", {1: 1}),
+    ([50, 24], [30, 31], 0, W.LIM_MPP, "sl", {1: 3}),
+    ([100, 24], [20, 25], 0, W.LIM_MPP, "sl", {1: 1}),
+    ([3, 3], [384, 320], 1, W.LIM_MPP, "sl", {2: 1}),
+    ([3, 3], [384, 300], 1, W.LIM_MPP, "sl", {2: 3}),
+]
+BIG = [
+    ([97, 48], [30, 31], 1, W.LIM_MPP, "sl", {1: 3}),
+    ([36, 128], [30, 31], 0, W.LIM_MPP, "sl", {1: 1}),
+    ([74, 74], [1, 3072], 0, W.LIM_MPP, "sl", {3: 1}),
+    ([73, 74], [1, 768], 0, W.LIM_MPP, "sl", {3: 3}),
+    ([36, 36], [24, 2160], 1, W.LIM_MPP, "sl", {2: 3}),
+    ([32, 36], [24, 2160], 1, W.LIM_MPP, "sl", {2: 2}),
+    ([36, 36], [24, 336], 1, W.LIM_MPP, "sl", {2: 2}),
 ]
 
 
@@ -46,7 +80,7 @@ def _dt(case, axis):
 
 
 @pytest.mark.parametrize("order", [5, 7])
-@pytest.mark.parametrize("case", CASES, ids=lambda c: f"{c[0]}x{c[1]}-{c[2]}-{c[3]}-{c[4]}")
+@pytest.mark.parametrize("case", CASES + BIG, ids=lambda c: f"{c[0]}x{c[1]}-{c[2]}-{c[3]}-{c[4]}")
 def test_route(case, order):
     desc = S.make_desc(_spec(case, order), case[2])
     for axis, route in case[5].items():
