@@ -34,7 +34,7 @@ constexpr int kUneven = 5;
 // read and one write of f).  (Entries computed in the kernel instead of read
 // from a table cost small grids more in registers than the launch for the
 // table: 64 x 128 FP64, x sweep 9.0 -> 11.5 us.)
-enum : int { LINE_ONE = 0, LINE_RK = 1, LINE_REPEAT = 2 };
+enum : int { LINE_ONE = 0, LINE_RK = 1, LINE_REPEAT = 2, LINE_SUMS = 3 };
 
 // Persistent workgroups over tiles of whole pencils, the next tile's data
 // loaded into registers before the current one is computed, as in
@@ -382,48 +382,46 @@ line_sweep_kernel(SweepArgs a, LinePlan pl, const PencilEntry<T>* __restrict__ t
         }
       }
     }
-    if constexpr (!BLK && MODE != LINE_RK) {
-      if (a.mom != nullptr) {
-        // row sums for the velocity moment: L lanes per tile row, as few as give
-        // every thread a row (fewer lanes add more and combine less), each its
-        // vectors of the row in double, compensated, combined in a fixed order
-        auto row_sums = [&](auto lanes) {
-          constexpr int L = decltype(lanes)::value;
-          const int q = tid % L;
-          for (int i = tid / L; i < n; i += blockDim.x / L) {
-            const T* row = tile + (i + G) * rs;
-            KSum v{0.0, 0.0};
-            auto add = [&](int c0, int c1) {
-              for (int c = c0; c < c1; c += L * VN) {
-                const V x = *reinterpret_cast<const V*>(row + c);
-                if (c + VN <= w.valid) {
-                  kadd(v, vsum(x));
-                } else {
+    if constexpr (MODE == LINE_SUMS) {
+      // row sums for the velocity moment: L lanes per tile row, as few as give
+      // every thread a row (fewer lanes add more and combine less), each its
+      // vectors of the row in double, compensated, combined in a fixed order
+      auto row_sums = [&](auto lanes) {
+        constexpr int L = decltype(lanes)::value;
+        const int q = tid % L;
+        for (int i = tid / L; i < n; i += blockDim.x / L) {
+          const T* row = tile + (i + G) * rs;
+          KSum v{0.0, 0.0};
+          auto add = [&](int c0, int c1) {
+            for (int c = c0; c < c1; c += L * VN) {
+              const V x = *reinterpret_cast<const V*>(row + c);
+              if (c + VN <= w.valid) {
+                kadd(v, vsum(x));
+              } else {
 #pragma unroll
-                  for (int m = 0; m < VN; ++m)
-                    if (c + m < w.valid) kadd(v, (double)x[m]);
-                }
+                for (int m = 0; m < VN; ++m)
+                  if (c + m < w.valid) kadd(v, (double)x[m]);
               }
-            };
-            // neighbouring rows begin at different vectors, on different banks
-            const int first = L < 16 && w.valid > 4 * L * VN ? (i & 3) * L * VN : 0;
-            add(first + q * VN, w.valid);
-            if (L < 16) add(q * VN, first);
-            if (L > 8) merge_dpp<kRowMirror>(v);
-            if (L > 4) merge_dpp<kHalfMirror>(v);
-            merge_dpp<kQuadReverse>(v);
-            merge_dpp<kPairSwap>(v);
-            if (q == 0) *reinterpret_cast<double2*>(a.mom + 2 * (t * n + i)) = make_double2(v.s, v.c);
-          }
-        };
-        if (4 * n >= (int)blockDim.x)
-          row_sums(std::integral_constant<int, 4>{});
-        else if (8 * n >= (int)blockDim.x)
-          row_sums(std::integral_constant<int, 8>{});
-        else
-          row_sums(std::integral_constant<int, 16>{});
-        __syncthreads();
-      }
+            }
+          };
+          // neighbouring rows begin at different vectors, on different banks
+          const int first = L < 16 && w.valid > 4 * L * VN ? (i & 3) * L * VN : 0;
+          add(first + q * VN, w.valid);
+          if (L < 16) add(q * VN, first);
+          if (L > 8) merge_dpp<kRowMirror>(v);
+          if (L > 4) merge_dpp<kHalfMirror>(v);
+          merge_dpp<kQuadReverse>(v);
+          merge_dpp<kPairSwap>(v);
+          if (q == 0) *reinterpret_cast<double2*>(a.mom + 2 * (t * n + i)) = make_double2(v.s, v.c);
+        }
+      };
+      if (4 * n >= (int)blockDim.x)
+        row_sums(std::integral_constant<int, 4>{});
+      else if (8 * n >= (int)blockDim.x)
+        row_sums(std::integral_constant<int, 8>{});
+      else
+        row_sums(std::integral_constant<int, 16>{});
+      __syncthreads();
     }
     // (otherwise no barrier: the next tile first writes this thread's own
     // vectors, at the offsets it has just read, and ghost cells)
@@ -457,6 +455,9 @@ hipError_t launch_l(const SweepArgs& a, const LinePlan& p, const void* table, hi
   }
   if (p.K && p.reps > 1) return launch_t<T, ORDER, LIM, true, LINE_REPEAT>(a, p, table, s);
   if (p.K) return launch_t<T, ORDER, LIM, true, LINE_ONE>(a, p, table, s);
+  if (a.mom)
+    return p.stream ? launch_t<T, ORDER, LIM, false, LINE_SUMS>(a, p, table, s)
+                    : launch_t<T, ORDER, LIM, false, LINE_SUMS, false>(a, p, table, s);
   return p.stream ? launch_t<T, ORDER, LIM, false, LINE_ONE>(a, p, table, s)
                   : launch_t<T, ORDER, LIM, false, LINE_ONE, false>(a, p, table, s);
 }
@@ -509,7 +510,8 @@ LinePlan plan_line(int dtype, int order, const SweepArgs& a, int64_t moment_bloc
   const bool blk = moment_block <= 0 && inner <= std::max(pwmax, 48) && inner * S <= threads &&
                    inner * percell + 32 * es <= (int64_t)kLineLdsMax && !(inner > 48 && waves(inner) == kUneven);
   // row tiles narrower than 64 bytes take longer segments
-  if (!blk && pwmax * es < 64 && Rt == 8 && maxr > 8 && !tile_of(threads, maxr)) return LinePlan{};
+  if (!blk && pwmax * es < 64 && Rt == 8 && maxr > 8 && cells >= ((int64_t)1 << 19) && !tile_of(threads, maxr))
+    return LinePlan{};
   if (blk && es == 8 && !a.rk) {
     const LinePlan wide = p;
     const int S0 = S, pw0 = pwmax;
@@ -547,7 +549,8 @@ LinePlan plan_line(int dtype, int order, const SweepArgs& a, int64_t moment_bloc
     p.bstride = moment_block > 0 ? moment_block : n * inner;
     // rows of whole 64-byte pieces where every row starts on one
     const int line = 64 / es;
-    const bool lines = inner % line == 0 && p.blen % line == 0;
+    const bool lines = inner % line == 0 && p.blen % line == 0 &&
+                       (moment_block <= 0 || cells * es > ((int64_t)1 << 25));
     int w = std::max(vn, pwmax / vn * vn);
     if (lines && w >= line) w = w / line * line;
     int64_t tpb = (p.blen + w - 1) / w;
