@@ -912,7 +912,7 @@ slmpp_status slmpp_create(const slmpp_grid_desc* desc, void* f_dev, void* work_d
     c->isolated = (desc->flags & SLMPP_FLAG_ISOLATED) != 0;
     if (e == hipSuccess && c->isolated) e = iso_setup(c, *desc);
     c->fplan = plan_field(c->D, desc->nx, c->hx, desc->poisson_order, c->isolated);
-    c->conv_field = c->D == 1 && c->nxs <= kConvMax;
+    c->conv_field = c->D == 1;
     if (e == hipSuccess && c->conv_field) {
       e = launch_conv_setup((int)c->nxs, c->hx[0], desc->poisson_order, c->green(), c->tw(), c->conv(),
                             c->stream);

@@ -320,9 +320,52 @@ __global__ void __launch_bounds__(128) field_force_kernel(FieldPlan p, const dou
 
 }  // namespace
 
+namespace {
+// Time of the solve in four launches: few workgroups transform long lines
+// where an axis is long and the others short.  A workgroup's transforms of
+// nin inputs take 37 ns per input and round of its threads (the latency of
+// a sum) or 9 per input and wavefront (the LDS of a CU; 12 where the outputs
+// wanted are some of the transform's), whichever is longer; four launches.
+double transforms_us(int lines, int nin, int m, int nout, int threads) {
+  const bool full = nout == m;
+  const int64_t sums = (int64_t)lines * (full ? m / (m % 4 == 0 ? 4 : m % 2 == 0 ? 2 : 1) : nout);
+  const double rounds = (double)((sums + threads - 1) / threads), waves = (double)((sums + 63) / 64);
+  return 1e-3 * nin * std::max(37.0 * rounds, (full ? 9.0 : 12.0) * waves);
+}
+double four_launches_us(const FieldPlan& p) {
+  auto groups = [](int total, int each) { return (total + each - 1) / each; };
+  auto turns = [](int workgroups) { return (workgroups + 255) / 256; };
+  double planes = 0.0;
+  for (int c = 0; c < p.n[2] && p.n[1] > 1; c += p.cols2)
+    planes += transforms_us(std::min(p.cols2, p.n[2] - c), p.n[1], p.m[1], p.m[1], 512);
+  for (int r = 0; r < p.m[1]; r += p.rows2) {
+    const int rows = std::min(p.rows2, p.m[1] - r);
+    planes += transforms_us(rows, p.n[2], p.m[2], p.m[2], 512) + transforms_us(rows, p.m[2], p.m[2], p.o[2], 512);
+  }
+  if (p.n[1] > 1) planes += transforms_us(p.o[2], p.m[1], p.m[1], p.o[1], 512);
+  return turns(groups(p.n[1] * p.n[2], p.cols1)) * transforms_us(p.cols1, p.n[0], p.m[0], p.m[0], 256) +
+         turns(p.m[0]) * planes +
+         turns(groups(p.o[1] * p.o[2], p.cols3)) * transforms_us(p.cols3, p.m[0], p.m[0], p.o[0], 256) + 14.0;
+}
+// Time of the solve in a launch per axis, one thread per output: 150 ns per
+// input, or 3 ps per product of the grid (1.3 where most of it is zero).
+//   us, measured with the launches per axis / in four launches (and the moment):
+// 64^2 69 / 27, 512^2 886 / 336, 4096 x 2 1312 / 1256, 4 x 3001 933 / 2284,
+// 64^3 375 / 278, 90^3 1114 / 871, 4 x 90^2 129 / 225, 3 x 100 x 80 119 / 131,
+// 8 x 8 x 256 99 / 78; isolated 64^3 1860 / 610, 128 x 8 x 8 178 / 38,
+// 8 x 8 x 128 95 / 138.
+double separate_launches_us(const FieldPlan& p) {
+  const double all = (double)p.m[0] * p.m[1] * p.m[2];
+  double t = 36.0;
+  for (int l = 0; l < 3; ++l)
+    if (p.m[l] > 1) t += 2e-3 * p.m[l] * std::max(150.0, (p.halo ? 1.3e-3 : 3e-3) * all);
+  return t;
+}
+}  // namespace
+
 // D axes of n cells each (periodic: transforms of n; isolated: of 2 n, with
-// three halo cells of the potential on both sides).  lds == 0: the planes do
-// not fit the LDS of a workgroup.
+// three halo cells of the potential on both sides).  ok == 0: the planes do
+// not fit the LDS of a workgroup, or launches per axis are faster.
 FieldPlan plan_field(int D, const int64_t* nx, const double* h, int order, bool isolated) {
   FieldPlan p{};
   p.D = D;
@@ -375,7 +418,7 @@ FieldPlan plan_field(int D, const int64_t* nx, const double* h, int order, bool 
   p.cols2 = (int)std::max<size_t>(1, std::min<size_t>(p.n[2], room / ec));
   p.rows2 = (int)std::max<size_t>(1, std::min<size_t>(p.m[1], room / er));
   p.lds2 = plane + std::max(p.cols2 * ec, p.rows2 * er);
-  p.ok = 1;
+  p.ok = four_launches_us(p) <= separate_launches_us(p) ? 1 : 0;
   return p;
 }
 
@@ -441,19 +484,26 @@ __device__ __forceinline__ void merge_lanes(KSum& v) {
 // workgroup, each workgroup with the whole density in LDS (from the row sums
 // of an x_1 sweep: every workgroup adds them all, the first one stores rho).
 // Only differences of the density enter (the kernels sum to zero), summed with
-// compensation, so that no force of the density on itself builds up.  One launch in place of transforms, Green
-// function, inverse, forces and tables in one workgroup: 256 cells took 25 us
-// and two launches for tables, now 6.8 us.
+// compensation, so that no force of the density on itself builds up.  One launch
+// in place of transforms, Green function, inverse, forces and tables: 256
+// cells took 25 us in one workgroup and two launches for tables, now 6.8 us.
 template <typename T, int ORDER>
 __global__ void __launch_bounds__(kConvThreads) field_conv_kernel(
     int n, const double* __restrict__ part, bool pairs, int nsub, double dvol,
     double* __restrict__ rho, double* __restrict__ phi, double* __restrict__ accel, const double* __restrict__ conv,
     FieldTables tabs) {
-  __shared__ double x[kConvMax], kp[kConvMax], ka[kConvMax];
+  extern __shared__ __align__(16) unsigned char smem[];
+  // the density and the kernels' first halves
+  const int half = n / 2;
+  double* x = reinterpret_cast<double*>(smem);
+  double* kp = x + n;
+  double* ka = kp + half + 1;
   const int tid = threadIdx.x;
-  for (int i = tid; i < n; i += kConvThreads) {
+  for (int i = tid; i <= half; i += kConvThreads) {
     kp[i] = conv[i];
     ka[i] = conv[n + i];
+  }
+  for (int i = tid; i < n; i += kConvThreads) {
     double r;
     if (part) {
       r = sum_rows(part, pairs, i, nsub, n, dvol);
@@ -507,8 +557,12 @@ __global__ void __launch_bounds__(kConvThreads) conv_setup_kernel(int n, double 
                                                          const double* __restrict__ green,
                                                          const double2* __restrict__ tw,
                                                          double* __restrict__ conv) {
-  __shared__ double g[kConvMax / 2 + 1], gs[kConvMax / 2 + 1], c[kConvMax], sn[kConvMax];
+  extern __shared__ __align__(16) unsigned char smem[];
   const int half = n / 2;
+  double* g = reinterpret_cast<double*>(smem);
+  double* gs = g + half + 1;
+  double* c = gs + half + 1;
+  double* sn = c + n;
   for (int q = threadIdx.x; q < n; q += blockDim.x) {
     const double2 t = tw[q <= half ? q : n - q];
     c[q] = t.x;
@@ -545,17 +599,23 @@ __global__ void __launch_bounds__(kConvThreads) conv_setup_kernel(int n, double 
 
 hipError_t launch_conv_setup(int n, double h, int order, const double* green, const double2* tw,
                              double* conv, hipStream_t s) {
+  const size_t lds = sizeof(double) * (2 * (size_t)(n / 2 + 1) + 2 * (size_t)n);
+  const hipError_t e = allow_lds(reinterpret_cast<const void*>(conv_setup_kernel), lds);
+  if (e != hipSuccess) return e;
   hipLaunchKernelGGL(conv_setup_kernel, dim3((n + kConvThreads / kConvLanes - 1) / (kConvThreads / kConvLanes)),
-                     dim3(kConvThreads), 0, s, n, h, order, green, tw, conv);
+                     dim3(kConvThreads), lds, s, n, h, order, green, tw, conv);
   return hipGetLastError();
 }
 
-hipError_t launch_field_conv(int n, const double* part, bool pairs, int nsub, double dvol, double* rho,
-                             double* phi, double* accel, const double* conv, int dtype, int order,
+hipError_t launch_field_conv(int n, const double* part, bool pairs, int nsub, double dvol,
+                             double* rho, double* phi, double* accel, const double* conv, int dtype, int order,
                              const FieldTables& tabs, hipStream_t s) {
   constexpr int per = kConvThreads / kConvLanes;
+  const size_t lds = sizeof(double) * ((size_t)n + 2 * (size_t)(n / 2 + 1));
   auto go = [&](auto kern) {
-    hipLaunchKernelGGL(kern, dim3((n + per - 1) / per), dim3(kConvThreads), 0, s, n, part, pairs, nsub, dvol, rho,
+    const hipError_t e = allow_lds(reinterpret_cast<const void*>(kern), lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kern, dim3((n + per - 1) / per), dim3(kConvThreads), lds, s, n, part, pairs, nsub, dvol, rho,
                        phi, accel, conv, tabs);
     return hipGetLastError();
   };

@@ -285,9 +285,8 @@ hipError_t launch_field_forward(const FieldPlan& p, const double* part, bool pai
 hipError_t launch_field_rest(const FieldPlan& p, double* phi, double* accel, double2* bufA,
                              double2* bufB, double* phi_ext, const double2* tw, const double* green,
                              int dtype, int order, const FieldTables& tabs, hipStream_t s);
-// D = 1, up to kConvMax cells: the whole solve as a convolution of the
-// density with conv[0..n) (potential) and conv[n..2n) (acceleration).
-constexpr int kConvMax = 1024;
+// D = 1: the whole solve as a convolution of the density with conv[0..n)
+// (potential) and conv[n..2n) (acceleration).
 hipError_t launch_conv_setup(int n, double h, int order, const double* green, const double2* tw,
                              double* conv, hipStream_t s);
 hipError_t launch_field_conv(int n, const double* part, bool pairs, int nsub, double dvol,
