@@ -600,6 +600,35 @@ __global__ void __launch_bounds__(256) velocity_distribution_kernel(const T* __r
       }
   }
 }
+// The same for few spatial cells: one thread per velocity cell.  Few threads
+// walk long columns here (one per velocity cell), so each keeps 16 loads in
+// flight: rows x = 16 m + r go to accumulator r % 4, merged in a fixed order.
+template <typename T>
+__global__ void __launch_bounds__(256) velocity_distribution_direct_kernel(const T* __restrict__ f,
+                                                                    int64_t nxs, int64_t nvs,
+                                                                    double xvol,
+                                                                    double* __restrict__ F) {
+  constexpr int U = 16;
+  for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < nvs;
+       k += (int64_t)gridDim.x * blockDim.x) {
+    KSum a[4] = {{0.0, 0.0}, {0.0, 0.0}, {0.0, 0.0}, {0.0, 0.0}};
+    const T* col = f + k;
+    int64_t ix = 0;
+    for (; ix + U <= nxs; ix += U) {
+      T x[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) x[u] = col[(ix + u) * nvs];
+#pragma unroll
+      for (int u = 0; u < U; ++u) kadd(a[u % 4], (double)x[u]);
+    }
+    for (; ix < nxs; ++ix) kadd(a[0], (double)col[ix * nvs]);
+    kmerge(a[0], a[1]);
+    kmerge(a[2], a[3]);
+    kmerge(a[0], a[2]);
+    F[k] = xvol * (a[0].s + a[0].c);
+  }
+}
+
 __global__ void __launch_bounds__(256) distribution_sum_kernel(const KSum* __restrict__ part,
                                                                int shares, int64_t nvs, double xvol,
                                                                double* __restrict__ F) {
@@ -1239,6 +1268,20 @@ hipError_t launch_velocity_moments(int dtype, const void* f, int D, const int64_
 hipError_t launch_velocity_distribution(int dtype, const void* f, int64_t nxs, int64_t nvs,
                                         double xvol, double* F, double* scratch,
                                         int64_t scratch_doubles, hipStream_t s) {
+  // Few spatial cells, or enough velocity cells for a thread each: one launch
+  // without shares.  us, directly / in vectors and shares: 64 x 8^2 x 128^2 FP32 3.8 /
+  // 7.7, 7^2 x 30x41 FP64 4.0 / 6.8, 22^2 x 128^2 FP32 15.6 / 20.8, 10^3 x 40^3 FP32
+  // 45 / 63, 12^3 x 32^3 FP64 101 / 90, 24^3 x 16x20x24 FP32 662 / 157.
+  if (nxs <= (nvs >= 32768 ? 2048 : nvs >= 12288 ? 512 : dtype == SLMPP_F64 ? 128 : 256)) {
+    const dim3 all((unsigned)std::min<int64_t>((nvs + 255) / 256, 4096));
+    if (dtype == SLMPP_F64)
+      hipLaunchKernelGGL(velocity_distribution_direct_kernel<double>, all, dim3(256), 0, s, (const double*)f,
+                         nxs, nvs, xvol, F);
+    else
+      hipLaunchKernelGGL(velocity_distribution_direct_kernel<float>, all, dim3(256), 0, s, (const float*)f,
+                         nxs, nvs, xvol, F);
+    return hipGetLastError();
+  }
   const int vn = dtype == SLMPP_F64 ? 2 : 4;
   const int64_t bx = std::min<int64_t>(((nvs + vn - 1) / vn + 255) / 256, 4096);
   // shares of the spatial cells: about 2048 workgroups in all, at least 16
