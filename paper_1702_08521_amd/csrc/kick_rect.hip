@@ -181,14 +181,11 @@ template <typename T, int ORDER>
 hipError_t launch_t(const SweepArgs& a, const RectPlan& p, const void* tabA, const void* tabB, hipStream_t s) {
   auto kern = kick_rect_kernel<T, ORDER>;
   const void* fn = reinterpret_cast<const void*>(kern);
-  int per_cu = 0, dev = 0, n_cu = 0;
-  hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, p.threads, p.lds_bytes);
-  if (e == hipSuccess) e = hipGetDevice(&dev);
-  if (e == hipSuccess) e = hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev);
-  if (e != hipSuccess) return e;
   // at most seven wavefronts per SIMD, as for the square planes
-  per_cu = std::min(per_cu, std::max(1, 28 / ((p.threads + 63) / 64)));
-  const int64_t grid = std::min<int64_t>(p.planes, (int64_t)std::max(per_cu, 1) * std::max(n_cu, 1));
+  int64_t grid = 0;
+  const hipError_t e =
+      resident_grid(fn, p.threads, p.lds_bytes, p.planes, std::max(1, 28 / ((p.threads + 63) / 64)), &grid);
+  if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(p.threads), p.lds_bytes, s, a, p,
                      reinterpret_cast<const PencilEntry<T>*>(tabA),
                      reinterpret_cast<const PencilEntry<T>*>(tabB));

@@ -84,6 +84,11 @@ struct TableJobs {
   }
 };
 hipError_t launch_tables(int dtype, int order, const TableJobs& jobs, hipStream_t s);
+// Workgroups of a persistent kernel for `tiles` tiles: as many as the device
+// holds at once, at most max_per_cu on each CU.  The number of CUs is asked for
+// once per device, and the occupancy only where there are more tiles than CUs.
+hipError_t resident_grid(const void* kernel, int threads, size_t lds_bytes, int64_t tiles, int max_per_cu,
+                         int64_t* grid);
 hipError_t launch_sweep(int dtype, int order, int limiter, const SweepArgs& a,
                         const SweepPlan& p, const void* table, hipStream_t s);
 size_t pencil_table_bytes(int dtype, int64_t count);

@@ -31,6 +31,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdint>
 
@@ -211,6 +212,30 @@ SweepPlan plan_sweep(int dtype, int order, int limiter, int32_t n, int64_t npen,
     p.lds_bytes = lds(W, false);
   }
   return p;
+}
+
+hipError_t resident_grid(const void* kernel, int threads, size_t lds_bytes, int64_t tiles, int max_per_cu,
+                         int64_t* grid) {
+  constexpr int kDevices = 64;
+  static std::atomic<int> cus[kDevices];
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  int n_cu = dev >= 0 && dev < kDevices ? cus[dev].load(std::memory_order_relaxed) : 0;
+  if (n_cu == 0) {
+    e = hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev);
+    if (e != hipSuccess) return e;
+    n_cu = std::max(n_cu, 1);
+    if (dev >= 0 && dev < kDevices) cus[dev].store(n_cu, std::memory_order_relaxed);
+  }
+  *grid = tiles;
+  if (tiles <= n_cu) return hipSuccess;
+  int per_cu = 0;
+  e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, lds_bytes);
+  if (e != hipSuccess) return e;
+  per_cu = std::max(1, std::min(per_cu, max_per_cu));
+  *grid = std::min<int64_t>(tiles, (int64_t)per_cu * n_cu);
+  return hipSuccess;
 }
 
 hipError_t launch_tables(int dtype, int order, const TableJobs& jobs, hipStream_t s) {

@@ -6,6 +6,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <climits>
 #include <cmath>
 #include <cstdint>
 
@@ -906,19 +907,10 @@ hipError_t launch_fast(const SweepArgs& a, const SweepPlan& p, const void* table
                                        (int)p.lds_bytes);
     if (e != hipSuccess) return e;
   }
-  int per_cu = 0;
-  hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-      &per_cu, reinterpret_cast<const void*>(kern), p.threads, p.lds_bytes);
+  int64_t grid = 0;
+  const hipError_t e =
+      resident_grid(reinterpret_cast<const void*>(kern), p.threads, p.lds_bytes, p.tiles, INT_MAX, &grid);
   if (e != hipSuccess) return e;
-  static int n_cu = 0;
-  if (n_cu == 0) {
-    int dev = 0;
-    e = hipGetDevice(&dev);
-    if (e == hipSuccess) e = hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev);
-    if (e != hipSuccess) return e;
-  }
-  const int64_t slots = (int64_t)std::max(per_cu, 1) * std::max(n_cu, 1);
-  const int64_t grid = std::min<int64_t>(p.tiles, slots);
   hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(p.threads), p.lds_bytes, s, a, p,
                      reinterpret_cast<const PencilEntry<T>*>(table));
   return hipGetLastError();
@@ -1034,24 +1026,15 @@ hipError_t launch_plane_u(const SweepArgs& a, const PlanePlan& p, const void* ta
     if (e != hipSuccess) return e;
   }
   constexpr int NT = PlaneShape<T, ORDER, N, PB>::threads;
-  int per_cu = 0;
-  hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-      &per_cu, reinterpret_cast<const void*>(kern), NT, p.lds_bytes);
-  if (e != hipSuccess) return e;
-  static int n_cu = 0;
-  if (n_cu == 0) {
-    int dev = 0;
-    e = hipGetDevice(&dev);
-    if (e == hipSuccess) e = hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev);
-    if (e != hipSuccess) return e;
-  }
   // at most seven wavefronts per SIMD: with all eight slots taken the 24^2
   // planes in twos took 390 against 319 us (24^3 x 20x24^2 FP32) and the 64^2
   // planes 207 against 180 us (15 runs of 32^2 x 64^2); 48^2 planes 20.8 ms
   // either way
   constexpr int kWaves = (NT + 63) / 64;
-  per_cu = std::min(per_cu, std::max(1, 28 / kWaves));
-  const int64_t grid = std::min<int64_t>(p.tiles, (int64_t)std::max(per_cu, 1) * std::max(n_cu, 1));
+  int64_t grid = 0;
+  const hipError_t e =
+      resident_grid(reinterpret_cast<const void*>(kern), NT, p.lds_bytes, p.tiles, std::max(1, 28 / kWaves), &grid);
+  if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(NT), p.lds_bytes, s, a, p,
                      reinterpret_cast<const PencilEntry<T>*>(tabA),
                      reinterpret_cast<const PencilEntry<T>*>(tabB));

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <climits>
 #include <cstdint>
 #include <type_traits>
 
@@ -435,12 +436,9 @@ hipError_t launch_t(const SweepArgs& a, const LinePlan& p, const void* table, hi
   hipError_t e = hipSuccess;
   if (p.lds_bytes > 64 * 1024)
     e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)p.lds_bytes);
-  int per_cu = 0, dev = 0, n_cu = 0;
-  if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, p.threads, p.lds_bytes);
-  if (e == hipSuccess) e = hipGetDevice(&dev);
-  if (e == hipSuccess) e = hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev);
+  int64_t grid = 0;
+  if (e == hipSuccess) e = resident_grid(fn, p.threads, p.lds_bytes, p.tiles, INT_MAX, &grid);
   if (e != hipSuccess) return e;
-  const int64_t grid = std::min<int64_t>(p.tiles, (int64_t)std::max(per_cu, 1) * std::max(n_cu, 1));
   hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(p.threads), p.lds_bytes, s, a, p,
                      reinterpret_cast<const PencilEntry<T>*>(table));
   return hipGetLastError();

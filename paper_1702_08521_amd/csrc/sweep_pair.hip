@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <climits>
 #include <cstdint>
 
 #include "slmpp_internal.hpp"
@@ -211,15 +212,12 @@ template <typename T, int ORDER, bool PERIODIC>
 hipError_t launch_t(const SweepArgs& a, const PairPlan& p, const void* tabA, const void* tabB, hipStream_t s) {
   auto kern = pair_sweep_kernel<T, ORDER, PERIODIC>;
   const void* fn = reinterpret_cast<const void*>(kern);
-  int per_cu = 0, dev = 0, n_cu = 0;
   hipError_t e = hipSuccess;
   if (p.lds_bytes > 64 * 1024)
     e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)p.lds_bytes);
-  if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, p.threads, p.lds_bytes);
-  if (e == hipSuccess) e = hipGetDevice(&dev);
-  if (e == hipSuccess) e = hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev);
+  int64_t grid = 0;
+  if (e == hipSuccess) e = resident_grid(fn, p.threads, p.lds_bytes, p.tiles, INT_MAX, &grid);
   if (e != hipSuccess) return e;
-  const int grid = std::min(p.tiles, std::max(per_cu, 1) * std::max(n_cu, 1));
   hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(p.threads), p.lds_bytes, s,
                      reinterpret_cast<T*>(a.f), (T)a.alpha, p,
                      reinterpret_cast<const PencilEntry<T>*>(tabA),
