@@ -49,6 +49,11 @@ def workload(name, dtype):
     raise SystemExit(f"unknown workload {name}")
 
 
+# what the bytes of a sweep depend on: its kernel, its plan and its dispatch
+TRAFFIC_SOURCES = ("sweep_device.hpp", "sweep_kernels.hpp", "sweep_launch.hpp", "slmpp_internal.hpp", "sweep.hip",
+                   "sweep_f32.hip", "api.hip")
+
+
 def read_traffic(kernel_key):
     """HBM traffic per launch from the committed counter summary, or None
     when the summary is absent or was taken on other kernel sources."""
@@ -65,7 +70,7 @@ def read_traffic(kernel_key):
     import hashlib
 
     h = hashlib.sha256()
-    for name in ("sweep_device.hpp", "sweep_kernels.hpp"):
+    for name in TRAFFIC_SOURCES:
         with open(os.path.join(ROOT, "paper_1702_08521_amd", "csrc", name), "rb") as src:
             h.update(src.read())
     if ent.get("sweep_src_sha") != h.hexdigest()[:16]:

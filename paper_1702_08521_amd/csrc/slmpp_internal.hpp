@@ -93,15 +93,6 @@ hipError_t launch_sweep(int dtype, int order, int limiter, const SweepArgs& a,
                         const SweepPlan& p, const void* table, hipStream_t s);
 size_t pencil_table_bytes(int dtype, int64_t count);
 
-// The last two velocity axes of one kick in one pass over f (outflow
-// velocity boundaries, SL-MPP, square planes of N = 24, 32, 48 or 64
-// cells): plane p = (x, v_1..v_{D-2}) is the contiguous block
-// f[p * N^2 .. (p + 1) * N^2); its pencils along v_{D-1} take table entry
-// tabA[p / vouter] and those along v_D tabB[p / vouter].  Several runs of
-// one geometry in one launch: SweepArgs::fmulti / tmulti / tpr (tiles per
-// run) with tmulti holding the v_{D-1} tables of the runs, then their v_D
-// tables; planes and tiles as for one run, times the number of runs for
-// tiles.
 // n / d for 32-bit n by an invariant 32-bit divisor d >= 1 (Granlund and
 // Montgomery, "Division by invariant integers using multiplication", 1994):
 // t = mulhi(m, n), n / d = (t + ((n - t) >> s1)) >> s2 with
@@ -124,6 +115,15 @@ struct FastDiv32 {
   }
 };
 
+// The last two velocity axes of one kick in one pass over f (outflow
+// velocity boundaries, SL-MPP, square planes of N = 24, 32, 48 or 64
+// cells): plane p = (x, v_1..v_{D-2}) is the contiguous block
+// f[p * N^2 .. (p + 1) * N^2); its pencils along v_{D-1} take table entry
+// tabA[p / vouter] and those along v_D tabB[p / vouter].  Several runs of
+// one geometry in one launch: SweepArgs::fmulti / tmulti / tpr (tiles per
+// run) with tmulti holding the v_{D-1} tables of the runs, then their v_D
+// tables; planes and tiles as for one run, times the number of runs for
+// tiles.
 struct PlanePlan {
   int32_t N, PB;       // plane side, planes per tile
   int32_t G, pitch;    // ring of zero cells around each plane in LDS, LDS row
@@ -135,8 +135,9 @@ struct PlanePlan {
   FastDiv32 vdiv;      // plane -> spatial cell (plane / vouter) while planes < 2^32
   size_t lds_bytes;    // 0: the shape is not supported
 };
-// Tiling of a sweep by line_sweep_kernel (any pencil length up to 2048, any
-// stride, limiter and time integration).  A tile is W pencils of one block
+// Tiling of a sweep by line_sweep_kernel: any limiter and stride, pencils of up
+// to 2048 cells (1024 with TVD-RK, whose workgroups have half the threads) while
+// a 16-byte vector of them fits the LDS.  A tile is W pencils of one block
 // of `blen` consecutive pencils (rows of W elements, `inner` apart), or, when
 // K > 0, K whole blocks of `inner` pencils each (contiguous in f).
 struct LinePlan {

@@ -32,10 +32,12 @@ constexpr int kPlaneFast = 4;  // integer shifts read directly in the plane kern
 // and 24^2 planes in twos (fours) of four 6-cell segments fill whole
 // wavefronts: at 24^3 x 20x24^2 the pass takes 307 us in FP32 with four planes
 // (319 with two, 357 with three of 8-cell segments, whose last wavefront is
-// 3/8 full) and 876 in FP64 with two (1062 with 8-cell segments).  FP64 32^2
-// planes in twos keep one segment per wavefront: 595 against 608 us at 20^3 x
-// 20x32^2 (530 with the kernel's compile-time data map), but 80 against 71 us at 132^2 x 32^2, where the planes of a tile
-// would not share their entries.
+// 3/8 full) and 876 in FP64 with two (1062 with 8-cell segments); in 2D, where a
+// tile's planes lie in different cells, a kick of 132^2 x 24^2 FP32 takes 78-81 us
+// in twos against 93-99 in threes of 8-cell segments.  FP64 32^2 planes in twos
+// keep one segment per wavefront: 595 against 608 us at 20^3 x 20x32^2 (530 with
+// the kernel's compile-time data map), but 80 against 71 us at 132^2 x 32^2, where
+// the planes of a tile would not share their entries.
 constexpr int plane_count(bool f64, int N, int64_t vouter) {
   return N == 24 ? (!f64 && vouter % 4 == 0 ? 4 : 2) : N == 32 ? (!f64 || vouter % 2 == 0 ? 2 : 1) : 1;
 }

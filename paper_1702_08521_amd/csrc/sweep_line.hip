@@ -32,7 +32,9 @@ constexpr int kUneven = 5;
 
 // MODE of line_sweep_kernel: one sweep; all three TVD-RK stages; pl.reps
 // sweeps of block tiles one after the other (the same kick twice, with one
-// read and one write of f).  (Entries computed in the kernel instead of read
+// read and one write of f); one sweep of row tiles that leaves the row sums of
+// the velocity moment (whose code took registers from the others: 24^6 FP32
+// SL-MP7 sweeps 2.36 against 2.34 ms).  (Entries computed in the kernel instead of read
 // from a table cost small grids more in registers than the launch for the
 // table: 64 x 128 FP64, x sweep 9.0 -> 11.5 us.)
 enum : int { LINE_ONE = 0, LINE_RK = 1, LINE_REPEAT = 2, LINE_SUMS = 3 };
@@ -57,8 +59,8 @@ enum : int { LINE_ONE = 0, LINE_RK = 1, LINE_REPEAT = 2, LINE_SUMS = 3 };
 // element-wise loads; the whole step 11.20 -> 6.42 ms), by its vector
 // instructions at about 40 per cell where f stays in the caches (24^6 FP32
 // SL-MP7: 414-523 us, was 650-700), by the latency of a tile on small grids
-// (256 x 512: 5.2 and 6.8 us, was 9).  48^2 x 40^2 FP64 RK-MPP5 step: 495 ->
-// 332 us.  What made it: registers for two workgroups per CU (one took
+// (256 x 512: 5.4 and 6.9 us, was 9).  48^2 x 40^2 FP64 RK-MPP5 step: 495 ->
+// 239 us.  What made it: registers for two workgroups per CU (one took
 // 11.9 ms for that step), steps between a thread's vectors kept in scalar
 // registers, and loads without a second path for partial vectors (whose
 // merge made every load wait for the one before: 7.34 ms).
