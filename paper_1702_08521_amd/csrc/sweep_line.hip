@@ -60,7 +60,7 @@ enum : int { LINE_ONE = 0, LINE_RK = 1, LINE_REPEAT = 2, LINE_SUMS = 3 };
 // instructions at about 40 per cell where f stays in the caches (24^6 FP32
 // SL-MP7: 414-523 us, was 650-700), by the latency of a tile on small grids
 // (256 x 512: 5.4 and 6.9 us, was 9).  48^2 x 40^2 FP64 RK-MPP5 step: 495 ->
-// 239 us.  What made it: registers for two workgroups per CU (one took
+// 304 us.  What made it: registers for two workgroups per CU (one took
 // 11.9 ms for that step), steps between a thread's vectors kept in scalar
 // registers, and loads without a second path for partial vectors (whose
 // merge made every load wait for the one before: 7.34 ms).
